@@ -264,7 +264,7 @@ SC_DEV WinBlock win_block(const AttnArgs& a, int bh, int qb) {
   wb.qb = qb;
   wb.h = wb.bh % a.H;
   wb.b = wb.bh / a.H;
-  wb.L = clampi(a.valid_len[wb.b], 0, a.n);
+  wb.L = __builtin_amdgcn_readfirstlane(clampi(a.valid_len[wb.b], 0, a.n));
   wb.q0 = wb.qb * QB;
   wb.kt0 = max(0, wb.q0 - a.r);
   wb.kt1 = min(wb.L, wb.q0 + QB + (a.causal ? 0 : a.r));  // causal: no key after the block's last query
@@ -1184,15 +1184,352 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
   }
 }
 
+
+// --------------------------------------------- bf16 pass 1, 32 queries a wave --
+// A wave owns 32 queries and takes a tile's keys in halves of 32 on the 32x32x16
+// products: against 16 queries a wave, each K fragment and V read feeds twice
+// the pairs, and the tile's address, load and max bookkeeping is spread over
+// twice as many.  The interior loop issues 3.3 VALU instructions per pair
+// and lane (an FMA, an exponential, an add, half a conversion), so it runs near
+// the VALU issue rate at three waves per SIMD (166 VGPRs); four waves per SIMD
+// (128 VGPRs, addresses recomputed) measured the same.  What is left is the
+// launch's tail (3.2 rounds of 20 us blocks at B8 n4096).
+constexpr int kBQ3 = 128;  // queries per block: 4 waves x 32
+
+// Logits of keys 32 h .. 32 h + 31 of a tile: S^T = K Q^T.  Lane l holds query
+// l % 32 and, in register i, key 32 h + 8 (i / 4) + 4 (l / 32) + i % 4.  kb: the
+// tile; koff[c]: byte offset of the lane's unit of dims 16 c.
+SC_DEV f32x16 qk_half3(const bf16x8 (&qf)[4], const char* kb, const int (&koff)[4], int h) {
+  f32x16 s = {};
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kb + koff[c] + 4096 * h), qf[c], s, 0,
+                                                0, 0);
+  return s;
+}
+
+// P = exp2(S c2 - m) of a half as bf16 operands, and the lane's own sum of P.
+SC_DEV float exp_half3(const f32x16& s, float c2, float m, bf16x8 (&pb)[2]) {
+  float ps[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    float p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = fast_exp2(fmaf(s[8 * c + i], c2, -m));
+    ps[c] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pb[c][i] = (__bf16)p[i];
+  }
+  return ps[0] + ps[1];
+}
+
+// Online softmax of a half's (masked) logits: P with the running max; when a
+// lane's sum of P passes 2^kTau the maxima are raised to the half's and P is
+// recomputed (as in softmax_tile2).
+SC_DEV void softmax_half3(const f32x16& s, float c2, float& m_use, float& l_run, f32x16 (&o)[2], bf16x8 (&pb)[2]) {
+  float part = exp_half3(s, c2, m_use, pb);
+  if (__builtin_amdgcn_ballot_w64(part > kRaiseSum) != 0ull) {
+    float mx = vmax(s[0], s[1]);
+#pragma unroll
+    for (int i = 2; i < 16; i += 2) mx = vmax(vmax(mx, s[i]), s[i + 1]);
+    const float tmax = xor32_max(mx) * c2;
+    const bool up = tmax > m_use;
+    const float f = up ? fast_exp2(m_use - tmax) : 1.0f;
+    m_use = up ? tmax : m_use;
+    l_run *= f;
+    o[0] *= f;
+    o[1] *= f;
+    part = exp_half3(s, c2, m_use, pb);
+  }
+  l_run += part;
+}
+
+// V operands of a half by transposed reads of the row-major tile, dims 32 dt of
+// keys 16 c in vf[2 c + dt]; voff[dt]: byte offset of the lane's 4 dims of row
+// 4 (l / 32) + (l % 16) / 4.  Read ahead of the half's softmax, whose raise
+// branch the compiler does not move reads across.
+SC_DEV void v_half3(const char* vb, const int (&voff)[2], int h, bf16x8 (&vf)[4]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) {
+      const i16x4 a0 = lds_read_tr16(vb + voff[dt] + 4096 * h + 2048 * c);
+      const i16x4 a1 = lds_read_tr16(vb + voff[dt] + 4096 * h + 2048 * c + 1024);
+      vf[2 * c + dt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+}
+
+// O^T += V^T P^T for a half.
+SC_DEV void pv_half3(const bf16x8 (&pb)[2], const bf16x8 (&vf)[4], f32x16 (&o)[2]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+      o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * c + dt], pb[c], o[dt], 0, 0, 0);
+}
+
+// Keys h of a tile that need no mask: logits, softmax and P V of both halves,
+// the second half's logits on the matrix cores during the first's softmax.
+SC_DEV void tile3(const bf16x8 (&qf)[4], const char* kb, const char* vb, const int (&koff)[4], const int (&voff)[2],
+                  float c2, float& m_use, float& l_run, f32x16 (&o)[2]) {
+  bf16x8 pb[2];
+  const f32x16 s0 = qk_half3(qf, kb, koff, 0);
+  const f32x16 s1 = qk_half3(qf, kb, koff, 1);
+  bf16x8 vf[4];
+  v_half3(vb, voff, 0, vf);
+  softmax_half3(s0, c2, m_use, l_run, o, pb);
+  pv_half3(pb, vf, o);
+  v_half3(vb, voff, 1, vf);
+  softmax_half3(s1, c2, m_use, l_run, o, pb);
+  pv_half3(pb, vf, o);
+}
+
+// The halves of a tile whose bit of `live` (wave-uniform) is set, after
+// mask(h, s) has set the disallowed logits of half h to -inf.
+template <typename MaskFn>
+SC_DEV void tile3_masked(const bf16x8 (&qf)[4], const char* kb, const char* vb, const int (&koff)[4],
+                         const int (&voff)[2], float c2, float& m_use, float& l_run, f32x16 (&o)[2], unsigned live,
+                         MaskFn mask) {
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h)
+    if ((live >> h) & 1u) {
+      bf16x8 pb[2];
+      f32x16 s = qk_half3(qf, kb, koff, h);
+      bf16x8 vf[4];
+      v_half3(vb, voff, h, vf);
+      mask(h, s);
+      softmax_half3(s, c2, m_use, l_run, o, pb);
+      pv_half3(pb, vf, o);
+    }
+}
+
+// Pass 1 for bf16: O, LSE and the log2 LSE of the block's kBQ3 queries.
+// Every query attends the keys of its band, and the global keys outside it.
+// The band tiles come first, masked by position alone (a global key inside a
+// query's band is one of its band keys); then the global keys, gathered 64
+// slots to a tile, each masked to the queries whose band does not hold it.
+SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
+  using T = __bf16;
+  const int h = bh % a.H, b = bh / a.H;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), gg = lane >> 5,
+            lq = lane & 31;
+  const int n = a.n, r = a.r, q0 = qb * kBQ3;
+  const int L = __builtin_amdgcn_readfirstlane(clampi(a.valid_len[b], 0, n));
+  T* Og = static_cast<T*>(a.out) + b * a.bs_out + h * kHeadDim;
+  float* lseg = a.lse ? a.lse + (long long)bh * n : nullptr;
+  float* l2g = a.win_lse2 ? a.win_lse2 + (long long)bh * n : nullptr;
+
+  if (q0 >= L) {  // padding block: zero output rows (unless the caller never reads them)
+    if (!a.skip_pad_out)
+      for (int c = tid; c < kBQ3 * 8; c += kThreads) {
+        const int q = q0 + (c >> 3);
+        if (q < n) zero16(Og + (long long)q * a.ld_out + 8 * (c & 7));
+      }
+    for (int i = tid; i < kBQ3; i += kThreads)
+      if (q0 + i < n) {
+        if (lseg) lseg[q0 + i] = -INFINITY;
+        if (l2g) l2g[q0 + i] = INFINITY;
+      }
+    return;
+  }
+  // reach of the band after the query: r, or 0 in the causal variant (where a
+  // global key after the query is not attended either)
+  const bool causal = a.causal != 0;
+  const int rh = causal ? 0 : r;
+  const int kt0 = max(0, q0 - r), kt1 = min(L, q0 + kBQ3 + rh);
+  const int nkt = (kt1 - kt0 + kBK - 1) / kBK;
+  const unsigned ldb = (unsigned)(2 * a.ld_in);
+  const T* Qg = static_cast<const T*>(a.q) + b * a.bs_in + h * kHeadDim;
+  const T* Kg = static_cast<const T*>(a.k) + b * a.bs_in + h * kHeadDim;
+  const T* Vg = static_cast<const T*>(a.v) + b * a.bs_in + h * kHeadDim;
+  const int* gpb = a.gpos && a.G > 0 ? a.gpos + (long long)b * a.G : nullptr;
+  const int G = gpb ? a.G : 0;
+  // direct loads of a tile: wave w fills rows 16w .. 16w + 15, 8 per load.
+  // Tiles below kt1 move the (scalar) base and keep the lanes' offsets; the
+  // last one repeats row kt1 - 1 past the range.
+  const int R0 = 16 * w + (lane >> 3);
+  const unsigned uk = 16u * ((lane & 7) ^ (lane >> 3)), uv = 16u * ((lane & 7) ^ v_swz(lane >> 3));
+  auto load_rows = [&](const T* g, __bf16* tile, unsigned u, int k0) {
+    const unsigned l0 = lds_addr(tile + 16 * w * 64), l1 = l0 + 1024u;
+    if (k0 + kBK <= kt1) {
+      const T* gb = g + (long long)k0 * a.ld_in;
+      lds_dma16(gb, (unsigned)R0 * ldb + u, l0);
+      lds_dma16(gb, (unsigned)(R0 + 8) * ldb + u, l1);
+    } else {
+      lds_dma16(g, (unsigned)min(k0 + R0, kt1 - 1) * ldb + u, l0);
+      lds_dma16(g, (unsigned)min(k0 + R0 + 8, kt1 - 1) * ldb + u, l1);
+    }
+  };
+  // the rows of 64 listed positions (unused entries, -1, load row 0)
+  auto load_list = [&](const T* g, __bf16* tile, unsigned u, const int* pos) {
+    const unsigned l0 = lds_addr(tile + 16 * w * 64), l1 = l0 + 1024u;
+    lds_dma16(g, (unsigned)max(pos[R0], 0) * ldb + u, l0);
+    lds_dma16(g, (unsigned)max(pos[R0 + 8], 0) * ldb + u, l1);
+  };
+  // slots of chunk c, one per lane (-1: unused)
+  auto slot_pos = [&](int c) {
+    const int p = kBK * c + lane < G ? gpb[kBK * c + lane] : -1;
+    return p < L ? max(p, -1) : -1;
+  };
+  // slots whose key lies outside the band of some query of the block
+  auto outside = [&](int p) {
+    return uniform64(__ballot(p >= 0 && (p < min(q0 + kBQ3, L) - 1 - r || (!causal && p > q0 + r))));
+  };
+  load_rows(Kg, sm.b[0], uk, kt0);
+  load_rows(Vg, sm.c[0], uv, kt0);
+  const int qa = q0 + 32 * w, qrow = qa + lq;
+  bf16x8 qf[4];
+  {
+    const T* qp = Qg + (long long)min(qrow, L - 1) * a.ld_in + 8 * gg;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) qf[c] = *reinterpret_cast<const bf16x8*>(qp + 16 * c);
+  }
+  // the first 64 slots; bit q of qglob: query qa + q is a global token
+  const int p0 = slot_pos(0);
+  const unsigned long long need0 = outside(p0);
+  unsigned qglob = 0u;
+  for (int c = 0; kBK * c < G; ++c) {
+    const int p = c == 0 ? p0 : slot_pos(c);
+    unsigned long long in = uniform64(__ballot(p >= qa && p < qa + 32));
+    for (; in != 0ull; in &= in - 1ull) qglob |= 1u << (__builtin_amdgcn_readlane(p, __builtin_ctzll(in)) - qa);
+  }
+  if (w == 0) sm.pos[0][lane] = p0;
+  const int ns = nkt + (need0 != 0ull ? 1 : 0);  // pipelined steps: the band tiles, then the first 64 slots
+
+  int koff[4], voff[2];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) koff[c] = 128 * lq + 16 * ((2 * c + gg) ^ (lq & 7));
+  {
+    const int lr = lane & 15, vr = 4 * gg + (lr >> 2);
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+      voff[dt] = 128 * vr + 16 * ((4 * dt + 2 * ((lane >> 4) & 1) + ((lr >> 1) & 1)) ^ v_swz(vr)) + 8 * (lr & 1);
+  }
+  const char* kbuf = reinterpret_cast<const char*>(&sm.b[0][0]);
+  const char* vbuf = reinterpret_cast<const char*>(&sm.c[0][0]);
+  float m_use = kNegBig, l_run = 0.f;
+  f32x16 o[2] = {};
+  // all vector loads so far (the first tiles, the query fragments) complete
+  // here; the compiler-visible wait keeps it from waiting for the query loads
+  // inside the tile loop, where the prefetch loads are in flight
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  wait_dma();
+  __syncthreads();
+
+  // Interior tiles [ia, ib) of this wave need no mask: every key of the tile
+  // lies in the band of all the wave's queries and below kt1.
+  const int ia = clampi(-((kt0 - (qa + 31 - r)) >> 6), 0, nkt);
+  const int ib = clampi(((min(qa + rh, kt1 - 1) - (kBK - 1) - kt0) >> 6) + 1, ia, nkt);
+  // a tile of 64 slots: a lane's query attends the keys outside its band
+  // (causal: before it)
+  auto global_tile = [&](const char* kb, const char* vb, const int* pos, unsigned long long need) {
+    const unsigned live = ((unsigned)need != 0u ? 1u : 0u) | ((need >> 32) != 0ull ? 2u : 0u);
+    tile3_masked(qf, kb, vb, koff, voff, a.c2, m_use, l_run, o, live, [&](int hf, f32x16& s) {
+      const int lo = qrow - r, hi = causal ? 0x7fffffff : qrow + r;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int4 p4 = *reinterpret_cast<const int4*>(pos + 32 * hf + 8 * m + 4 * gg);
+        const int p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s[4 * m + e] = ((p[e] < lo) | (p[e] > hi)) & (p[e] >= 0) ? s[4 * m + e] : -INFINITY;
+      }
+    });
+  };
+  // Step t computes from buffers t & 1 while the next step's K and V arrive in
+  // the others.
+  for (int t = 0; t < ns; ++t) {
+    const char* kb = kbuf + 8192 * (t & 1);
+    const char* vb = vbuf + 8192 * (t & 1);
+    if (t + 1 < nkt) {
+      load_rows(Kg, sm.b[(t + 1) & 1], uk, kt0 + (t + 1) * kBK);
+      load_rows(Vg, sm.c[(t + 1) & 1], uv, kt0 + (t + 1) * kBK);
+    } else if (t + 1 < ns) {
+      load_list(Kg, sm.b[(t + 1) & 1], uk, sm.pos[0]);
+      load_list(Vg, sm.c[(t + 1) & 1], uv, sm.pos[0]);
+    }
+    if (t >= ia && t < ib) {
+      tile3(qf, kb, vb, koff, voff, a.c2, m_use, l_run, o);
+    } else if (t < nkt) {
+      // halves that hold a key some query of the wave reaches; a half's mask
+      // is one-sided unless both band edges lie in it
+      const int k0 = kt0 + t * kBK, reach_lo = qa - r, reach_hi = min(qa + 31 + rh, kt1 - 1);
+      const unsigned live = (k0 <= reach_hi && k0 + 31 >= reach_lo ? 1u : 0u) |
+                            (k0 + 32 <= reach_hi && k0 + 63 >= reach_lo ? 2u : 0u);
+      tile3_masked(qf, kb, vb, koff, voff, a.c2, m_use, l_run, o, live, [&](int hf, f32x16& s) {
+        const int kh = k0 + 32 * hf, lo = qrow - r - 4 * gg - kh, hi = min(qrow + rh, kt1 - 1) - 4 * gg - kh;
+        if (kh < qa + 31 - r) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) >= lo ? s[i] : -INFINITY;
+        }
+        if (kh + 31 > min(qa + rh, kt1 - 1)) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) <= hi ? s[i] : -INFINITY;
+        }
+      });
+    } else {
+      global_tile(kb, vb, sm.pos[0], need0);
+    }
+    if (t + 1 < ns) wait_dma();
+    __syncthreads();
+  }
+  // further slots (more than 64; not pipelined)
+  for (int c = 1; kBK * c < G; ++c) {
+    const int p = slot_pos(c);
+    const unsigned long long need = outside(p);
+    if (need == 0ull) continue;
+    if (w == 0) sm.pos[1][lane] = p;
+    __syncthreads();
+    load_list(Kg, sm.b[0], uk, sm.pos[1]);
+    load_list(Vg, sm.c[0], uv, sm.pos[1]);
+    wait_dma();
+    __syncthreads();
+    global_tile(kbuf, vbuf, sm.pos[1], need);
+    __syncthreads();
+  }
+
+  const float l_row = xor32_sum(l_run);
+  const bool qin = qrow < L;
+  const bool qvalid = qin && !((qglob >> lq) & 1u);
+  const float lse2 = m_use + fast_log2(l_row);
+  const float inv = 1.0f / l_row;
+  // the two lanes of a query exchange 4-dim halves, so that each stores 16
+  // bytes: lane group 0 the dims 16m .. +7 of a 32-dim half, group 1 16m + 8 .. +15
+  if (qvalid || (!qin && qrow < n)) {
+    T* op = Og + (long long)qrow * a.ld_out + 8 * gg;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        uint32_t x[2], y[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          x[e] = pack_bf16(o[dt][8 * m + 2 * e] * inv, o[dt][8 * m + 2 * e + 1] * inv);
+          y[e] = pack_bf16(o[dt][8 * m + 4 + 2 * e] * inv, o[dt][8 * m + 5 + 2 * e] * inv);
+        }
+        const auto r0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+        const auto r1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+        const uint4 v = make_uint4(r0[0], r1[0], r0[1], r1[1]);
+        *reinterpret_cast<uint4*>(op + 32 * dt + 16 * m) = qin ? v : make_uint4(0, 0, 0, 0);
+      }
+    if (gg == 0 && lseg) lseg[qrow] = qin ? lse2 * kLn2 : -INFINITY;
+  }
+  // excluded rows (global or padding) get +inf: their column-sum probabilities are 0
+  if (gg == 0 && l2g && qrow < n) l2g[qrow] = qvalid ? lse2 : INFINITY;
+}
+
 // Work of launch 1 per (sequence, head) pair and key span: kSpanQB window
 // blocks, then the span's global-row blocks (one per 32-slot group).
-static_assert(kBQ == kBQ2 && kGlobalKeySpan % kBQ == 0, "window blocks tile the key span");
-constexpr int kSpanQB = kGlobalKeySpan / kBQ;
+static_assert(kBQ == kBQ2 && kGlobalKeySpan % kBQ == 0 && kGlobalKeySpan % kBQ3 == 0,
+              "window blocks tile the key span");
 struct FwdSpan {
   int per;  // blocks per span
 };
 
-__host__ __device__ inline FwdSpan fwd_span(const AttnArgs& a) { return {kSpanQB + (a.n_gr > 0 ? a.ngc : 0)}; }
+template <int BQ>
+__host__ __device__ inline FwdSpan fwd_span(const AttnArgs& a) {
+  return {kGlobalKeySpan / BQ + (a.n_gr > 0 ? a.ngc : 0)};
+}
 
 // Launch 1: the window pass-1 blocks and the global-row forward blocks (when
 // there are global tokens).  Span by span (a.span_major: sequences up to
@@ -1204,34 +1541,31 @@ __host__ __device__ inline FwdSpan fwd_span(const AttnArgs& a) { return {kSpanQB
 // Otherwise (longer sequences) the window blocks come first, pair by pair
 // (xcd_pair_map), and the global-row blocks last, where they fill the window
 // blocks' uneven tail.
-template <int DT>
+// BQ: queries per window block.
+template <int DT, int BQ>
 __global__ __launch_bounds__(kThreads) SC_OCC(DT == 1 ? 3 : 2) void k_attn_fwd(AttnArgs a) {
   __shared__ Smem<DT> sm;
   extern __shared__ uint32_t sDyn[];
-  if (!a.span_major) {
+  constexpr int kSpanQB = kGlobalKeySpan / BQ;
+  int bh, qb, gr = -1;  // a window block, or (gr >= 0) a global-row block
+  if (a.span_major) {
+    int c, o;
+    xcd_span_map(blockIdx.x, a.nkc, fwd_span<BQ>(a).per, a.H * a.B, bh, c, o);
+    if (o >= kSpanQB) gr = (bh * a.ngc + (o - kSpanQB)) * a.nkc + c;
+    qb = c * kSpanQB + o;
+  } else {
     const int nwin = a.nqb * a.H * a.B;
-    if ((int)blockIdx.x >= nwin) {
-      gr_fwd_block<DT>(a, blockIdx.x - nwin, sm);
-      return;
-    }
-    int bh, qb;
+    if ((int)blockIdx.x >= nwin) gr = blockIdx.x - nwin;
     xcd_pair_map(blockIdx.x, a.nqb, a.H * a.B, bh, qb);
-    if constexpr (DT == 1)
-      window_fwd_v2(a, bh, qb, sm, sDyn);
-    else
-      window_fwd_block<DT>(a, bh, qb, sm, sDyn);
+  }
+  if (gr >= 0) {
+    gr_fwd_block<DT>(a, gr, sm);
     return;
   }
-  const FwdSpan f = fwd_span(a);
-  int bh, c, o;
-  xcd_span_map(blockIdx.x, a.nkc, f.per, a.H * a.B, bh, c, o);
-  if (o >= kSpanQB) {
-    gr_fwd_block<DT>(a, (bh * a.ngc + (o - kSpanQB)) * a.nkc + c, sm);
-    return;
-  }
-  const int qb = c * kSpanQB + o;
   if (qb >= a.nqb) return;  // the last span's missing query blocks
-  if constexpr (DT == 1)
+  if constexpr (DT == 1 && BQ == kBQ3)
+    window_fwd_v3(a, bh, qb, sm);
+  else if constexpr (DT == 1)
     window_fwd_v2(a, bh, qb, sm, sDyn);
   else
     window_fwd_block<DT>(a, bh, qb, sm, sDyn);
@@ -2106,6 +2440,18 @@ int profile_read(double* fwd_ms, double* cols_ms, long long cap, long long* call
 // L2 in the pair order.
 constexpr int kSpanOrderMaxN = 4096;
 
+// bf16 window blocks of 128 queries for sequences padded to this length or
+// more.  A 128-query block issues a third fewer VALU instructions per pair
+// (21.6M against 32.4M per launch at B8 n4096), which counts where a launch
+// has several rounds of blocks; in a launch of one round the 64-query blocks
+// finish sooner.  The rule looks at n alone, so that a sequence's result does
+// not depend on the batch it comes in.  Launch 1 between events, us, 64 and
+// 128 queries (H12): B8 n4096 window 512 with 32 slots 92.5 and 83.6, causal
+// 74.2 and 65.6, B2 H16 n8192 window 1024 with 64 slots 118.7 and 110.3, B1
+// n4096 24.4 and 24.4; but B1 n2048 17.9 and 19.8, B1 n1024 window 256 12.5
+// and 15.4 (B64 n1024 80.7 and 75.2).
+constexpr int kWideMinN = 3072;
+
 template <int DT>
 static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   AttnArgs a = a0;
@@ -2117,20 +2463,21 @@ static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   a.n_bcol = cols ? a.nkb * a.H * a.B : 0;
   a.n_gcol = (cols && glob) ? a.nqr * a.ngc * a.H * a.B : 0;
   const int nxc = glob ? (a.G + kBK - 1) / kBK : 0;
-  if (DT == 1) {  // bf16 pass 1 runs kBQ2-query blocks
-    a.nqb = (a.n + kBQ2 - 1) / kBQ2;
-    const long long rw = (long long)kBQ2 + 2LL * a.r;
-    a.rwp = (int)(rw < a.n ? rw : a.n);
-  }
-  const size_t dyn = sizeof(uint32_t) * ((size_t)a.rwp / 32 + 2 + nxc + 1);
-  // the spans' block counts (the host checks that they fit the grid limits)
   const long long pairs = (long long)a.H * a.B;
-  const unsigned fwd_blocks = (unsigned)(a.span_major ? a.nkc * fwd_span(a).per * pairs : a.n_gr + a.nqb * pairs);
+  const bool wide = DT == 1 && a.n >= kWideMinN;
+  if (wide) a.nqb = (a.n + kBQ3 - 1) / kBQ3;
+  const size_t dyn = wide ? 0 : sizeof(uint32_t) * ((size_t)a.rwp / 32 + 2 + nxc + 1);
+  // the spans' block counts (the host checks that they fit the grid limits)
+  const int fwd_per = wide ? fwd_span<kBQ3>(a).per : fwd_span<kBQ>(a).per;
+  const unsigned fwd_blocks = (unsigned)(a.span_major ? a.nkc * fwd_per * pairs : a.n_gr + a.nqb * pairs);
   const int col_per = a.bp_band ? col_span<DT, true>(a).per : col_span<DT, false>(a).per;
   const unsigned col_blocks = (unsigned)(a.span_major ? a.nkc * col_per * pairs
                                                       : ((a.n_gr + 7) & ~7) + a.n_bcol + a.n_gcol);
   if (!a.no_profile) profile_mark(s, 0);
-  hipLaunchKernelGGL(k_attn_fwd<DT>, dim3(fwd_blocks), dim3(kThreads), dyn, s, a);
+  if (wide)
+    hipLaunchKernelGGL((k_attn_fwd<DT, DT == 1 ? kBQ3 : kBQ>), dim3(fwd_blocks), dim3(kThreads), dyn, s, a);
+  else
+    hipLaunchKernelGGL((k_attn_fwd<DT, kBQ>), dim3(fwd_blocks), dim3(kThreads), dyn, s, a);
   if (!a.no_profile) profile_mark(s, 1);
   if (col_blocks > 0) {
     if (a.bp_band)

@@ -17,10 +17,17 @@ namespace sc {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int kHeadDim = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+
+SC_DEV uint32_t pack_bf16(float lo, float hi) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+  return __builtin_bit_cast(uint32_t, v);
+}
 
 SC_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -143,6 +150,12 @@ SC_DEV void xcd_span_map(int i, int nspan, int per, int pairs, int& pair, int& c
   }
 }
 
+// XOR applied to the 16-byte unit index of row `row` of a value tile read by
+// the transposed reads of 32x32 products: a 32-lane phase of those reads
+// touches 4 rows and 4 units of each, one of 16x16 products 8 rows and 2 units;
+// even (and odd) rows share 32 banks, and this order keeps both free of conflicts.
+SC_DEV int v_swz(int row) { return ((row & 2) << 1) | ((row & 4) >> 1); }
+
 template <int DT>
 struct Tr;
 
@@ -211,6 +224,12 @@ SC_DEV void copy16(T* dst, const T* src) {
 template <typename T>
 SC_DEV void zero16(T* dst) {
   *reinterpret_cast<uint4*>(dst) = make_uint4(0, 0, 0, 0);
+}
+
+// A wave-uniform 64-bit value in scalar registers.
+SC_DEV unsigned long long uniform64(unsigned long long v) {
+  return (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v) |
+         ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32)) << 32);
 }
 
 SC_DEV int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }

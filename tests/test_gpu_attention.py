@@ -414,3 +414,33 @@ def test_dispatch_order_invariance(causal):
         assert np.array_equal(res[0][1][b, :, :L], res[1][1][b, :, :L]), f"lse of sequence {b} differs"
         assert np.array_equal(res[0][2][b, :L], res[1][2][b, :L]), f"scores of sequence {b} differ"
     log(f"dispatch orders bit-identical (causal {causal})")
+
+
+@pytest.mark.parametrize("n,lens,window,G,causal", [
+    (3072, (3072, 1, 129, 33), 33, 3, 0),        # odd window; a sequence of one token, one query in a second block
+    (3073, (3073, 0, 128, 97), 16, 70, 0),       # one query in the last block; two 64-slot tiles; an empty sequence
+    (3100, (3100, 300, 65, 31), 64, 33, 0),      # 33 slots: one in the second half of a tile; band edges on halves
+    (3072, (1000, 257, 130, 64), 0, 130, 0),     # window 0; three 64-slot tiles
+    (3075, (260, 700, 2, 500), 2000, 64, 0),     # the window covers the sequences: no key outside a band
+    (3072, (3071, 1500, 700, 160), 400, 5, 0),   # interior tiles between the edges
+    (3100, (3100, 300, 130, 1), 64, 70, 1),
+    (3072, (2999, 257, 96, 0), 33, 0, 1),
+])
+def test_wide_query_blocks(n, lens, window, G, causal):
+    """The 128-query window blocks (sequences padded to 3072 tokens or more): lengths at their edges, band edges
+    inside and between the 32-key halves, global keys inside and outside the bands.  Logits of order one (inputs
+    N(0, 1)), so that a key too many or too few moves the LSE beyond its tolerance."""
+    cfg = si.AttnConfig("wide", 31, 4, n, 2, 64, "bf16", window, (n, n), G, "random", input_scale=1.0)
+    inp = si.make_attention_inputs(cfg)
+    vl = np.array(lens, dtype=np.int32)
+    inp["valid_len"], inp["global_pos"] = vl, si.global_positions(31, vl, G, "random")
+    d = make_desc(inp)
+    d.causal = causal
+    q, k, v = (to_dev_storage(inp[x], "bf16") for x in ("q", "k", "v"))
+    out, lse, sp, _ = sc.sc_window_attention(d, q, k, v)
+    scores = sc.sc_ltp_score(d, sp)
+    ro, rl, rs = oracle.sparse_attention(inp["q64"], inp["k64"], inp["v64"], vl, inp["global_pos"], window,
+                                         inp["alpha"], causal=bool(causal))
+    check_out(out.float().cpu().numpy(), ro, "bf16", bf16_step=True)
+    check_lse(lse.cpu().numpy(), rl, vl)
+    check_scores(scores.cpu().numpy(), rs, vl)
