@@ -139,7 +139,8 @@ hipError_t launch_prune_gather(const PruneArgs& p, const GatherArgs& g, hipStrea
 
 // Stack pieces.
 // y[rows, N] = x[rows, K] . W[K, N] (bf16 in, fp32 accumulate), rows of
-// sequence b limited to len[b] (others untouched); output bf16 or fp32.
+// sequence b limited to len[b] (others untouched); output bf16 or fp32.  xidx
+// ([B, n] or NULL): row j of sequence b takes x's row xidx[b, j] instead of j.
 // GEMM epilogues: bf16 store, fp32 store, GELU then bf16 store.  The
 // surviving rows of all sequences are packed into shared row tiles on the
 // device (B <= kPackMaxB).
@@ -151,12 +152,12 @@ constexpr int kGemmBf16 = 0, kGemmF32 = 1, kGemmGeluBf16 = 2;
 constexpr int kGemmSplitRows = 128 * 128;
 constexpr int kPackMaxB = 8192;
 hipError_t launch_gemm_bf16(const void* x, const void* w, void* y, int mode, int B, int n, int K, int N,
-                            const int* len, float* part, hipStream_t s);
+                            const int* len, const int* xidx, float* part, hipStream_t s);
 // y = bf16(LayerNorm(x_res + t)) per row, rows of sequence b < len[b]; t or,
 // when part is not NULL, the slabs of the product of reduction length K that
-// wrote it.  B <= kPackMaxB.
+// wrote it.  xidx: as for the products, for x_res.  B <= kPackMaxB.
 hipError_t launch_residual_layernorm(const void* x_res, const float* t, void* y, int B, int n, int D, float eps,
-                                     const int* len, const float* part, int K, hipStream_t s);
+                                     const int* len, const int* xidx, const float* part, int K, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // Bits of the device-side descriptor check (the same values as SC_VALID_* in
 // sc.h): a length outside [0, n]; a global position below -1 or not below

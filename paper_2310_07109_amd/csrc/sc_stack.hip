@@ -68,7 +68,7 @@ SC_DEV float gelu_exact(float v) {
 
 __global__ __launch_bounds__(256) void k_gemm_bf16(const __bf16* __restrict__ X, const __bf16* __restrict__ W,
                                                    void* __restrict__ Y, int mode, int n, int K, int N,
-                                                   const int* __restrict__ len) {
+                                                   const int* __restrict__ len, const int* __restrict__ xidx) {
   __shared__ __attribute__((aligned(16))) __bf16 sX[kBM * kGPitch];
   __shared__ __attribute__((aligned(16))) __bf16 sW[kBN * kGPitch];  // transposed: [col][k]
   const int b = blockIdx.z;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const __bf16* __restrict__ X,
       const int m = m0 + row;
       __bf16* d = sX + row * kGPitch + 8 * part;
       if (m < rows && k0 + 8 * part < K)
-        copy16(d, Xb + (long long)m * K + k0 + 8 * part);
+        copy16(d, Xb + (long long)(xidx ? xidx[(long long)b * n + m] : m) * K + k0 + 8 * part);
       else
         zero16(d);
     }
@@ -258,11 +258,13 @@ SC_DEV void gemm_store(void* Y, long long off, float v) {
 
 // One output tile of BM x 128 (4 waves of BM/2 x 64, BM = 64, 128, 256) over this block's
 // stages s0 .. s1-1, kNBuf stage buffers with kNBuf - 1 stages in flight;
-// grow[r] = global row of tile row r (-1: past the packed rows).  slab: the
+// grow[r] = global row of tile row r (-1: past the packed rows), xrow[r] = the
+// row of X it comes from (any valid row past the packed ones).  slab: the
 // split's partial sums of this tile (row r at slab + r N), else NULL.
 template <int BM, int kNBuf, int kMode>
 SC_DEV void gemm_tile(const __bf16* __restrict__ X, const __bf16* __restrict__ W, void* __restrict__ Y,
-                      char* stage, const int* grow, int K, int N, int n0, int s0, int s1, float* slab) {
+                      char* stage, const int* grow, const int* xrow, int K, int N, int n0, int s0, int s1,
+                      float* slab) {
   constexpr int FI = BM / 32;        // 16-row fragments per wave (wave tile BM/2 x 64)
   constexpr int XL = BM / 64;        // X loads per wave and stage (16 rows each)
   constexpr int kDmaPerStage = XL + 2;
@@ -274,13 +276,12 @@ SC_DEV void gemm_tile(const __bf16* __restrict__ X, const __bf16* __restrict__ W
             lr = lane & 15;
   const int wm = (w >> 1) * (BM / 2), wn = (w & 1) * 64;
   const unsigned xrow_b = 2u * (unsigned)K, wrow_b = 2u * (unsigned)N;  // byte offsets fit in 32 bits (host)
-  // this lane's X rows (global, rows past the packed ones re-read the tile's first row)
+  // this lane's X rows
   unsigned xoff[XL];
 #pragma unroll
   for (int t = 0; t < XL; ++t) {
     const int R = (BM / 4) * w + 16 * t + lane / kXUnits;
-    const int gr = grow[R];
-    xoff[t] = (unsigned)(gr >= 0 ? gr : grow[0]) * xrow_b;
+    xoff[t] = (unsigned)xrow[R] * xrow_b;
   }
   auto issue = [&](int k0, int bf) {
     const int ln = opaque_lane();
@@ -363,7 +364,9 @@ SC_DEV void gemm_tile(const __bf16* __restrict__ X, const __bf16* __restrict__ W
 }
 
 // Y[row, N] = X[row, K] . W[K, N] over the surviving rows of the B
-// sequences (row j of sequence b at b n + j, j < len[b]).  part: float32
+// sequences (row j of sequence b at b n + j, j < len[b]); with xidx, row j of
+// sequence b reads X at row b n + xidx[b n + j] (the survivors of a pruning,
+// not compacted).  part: float32
 // slabs of a split reduction (kGemmF32 only), NULL for none.  Items (packed
 // tile t, N tile, K range ks), ks fastest, are dealt to the XCDs in
 // contiguous ranges (workgroup i runs on XCD i % 8): an XCD keeps its tiles'
@@ -373,9 +376,9 @@ SC_DEV void gemm_tile(const __bf16* __restrict__ X, const __bf16* __restrict__ W
 template <int kMode>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gemm_v3(const __bf16* __restrict__ X, const __bf16* __restrict__ W,
                                                  void* __restrict__ Y, int B, int n, int K, int N,
-                                                 const int* __restrict__ len, float* __restrict__ part) {
+                                                 const int* __restrict__ len, const int* __restrict__ xidx, float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) char stage[kStageBytes];
-  __shared__ int grow[256];
+  __shared__ int grow[256], xrow[256];
   int* pre = reinterpret_cast<int*>(stage);  // until the first stage lands
   pack_prefix(pre, len, B, n);
   __syncthreads();
@@ -388,23 +391,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   const int ks = (int)(item % pl.S), nt = (int)(item / pl.S % Nt), t = (int)(item / pl.S / Nt);
   const int m0 = t * pl.bm;
   if ((int)threadIdx.x < pl.bm) {
-    const int p = m0 + threadIdx.x;
-    int gr = -1;
-    if (p < R) {
-      const int b = pack_seq(pre, B, p);
-      gr = b * n + (p - pre[b]);
-    }
-    grow[threadIdx.x] = gr;
+    const int p = min(m0 + (int)threadIdx.x, R - 1);  // rows past the packed ones read the last row
+    const int b = pack_seq(pre, B, p);
+    const int gr = b * n + (p - pre[b]);
+    grow[threadIdx.x] = m0 + (int)threadIdx.x < R ? gr : -1;
+    xrow[threadIdx.x] = xidx ? b * n + clampi(xidx[gr], 0, n - 1) : gr;
   }
   __syncthreads();  // the prefix table is dead from here: the stages overwrite it
   const int per = nk / pl.S, s0 = ks * per, s1 = s0 + per;
   float* slab = pl.S > 1 ? part + ((long long)ks * pl.T * 128 + m0) * N : nullptr;
   if (pl.bm == 256)
-    gemm_tile<256, 2, kMode>(X, W, Y, stage, grow, K, N, nt * kBN, s0, s1, nullptr);
+    gemm_tile<256, 2, kMode>(X, W, Y, stage, grow, xrow, K, N, nt * kBN, s0, s1, nullptr);
   else if (pl.bm == 128)
-    gemm_tile<128, 3, kMode>(X, W, Y, stage, grow, K, N, nt * kBN, s0, s1, slab);
+    gemm_tile<128, 3, kMode>(X, W, Y, stage, grow, xrow, K, N, nt * kBN, s0, s1, slab);
   else
-    gemm_tile<64, 4, kMode>(X, W, Y, stage, grow, K, N, nt * kBN, s0, s1, nullptr);
+    gemm_tile<64, 4, kMode>(X, W, Y, stage, grow, xrow, K, N, nt * kBN, s0, s1, nullptr);
 }
 
 // v[4u + q] = x[c + q] + t[c + q] for the columns c = 4 lane + 256 u .. +3
@@ -438,11 +439,13 @@ SC_DEV void ln_load(float (&v)[kPer], const __bf16* xp, const float* tp, long lo
 }
 
 // One row of the residual LayerNorm: y = bf16(LayerNorm(x + t)) at global
-// row `row`, packed index p (where a split product left its partial sums).
+// row `row`, packed index p (where a split product left its partial sums), x
+// being row xrow of xr.
 template <int kMaxPer>
 SC_DEV void ln_row(const __bf16* __restrict__ xr, const float* __restrict__ t, __bf16* __restrict__ y, int D,
-                   float eps, const float* __restrict__ part, const GemmPlan& pl, long long row, int p, int lane) {
-  const __bf16* xp = xr + row * D;
+                   float eps, const float* __restrict__ part, const GemmPlan& pl, long long row, long long xrow, int p,
+                   int lane) {
+  const __bf16* xp = xr + xrow * D;
   __bf16* yp = y + row * D;
   float v[kMaxPer];
   if (pl.S == 1) {
@@ -490,8 +493,8 @@ SC_DEV void ln_row(const __bf16* __restrict__ xr, const float* __restrict__ t, _
 template <int kMaxPer>
 __global__ __launch_bounds__(256) void k_residual_ln(const __bf16* __restrict__ xr, const float* __restrict__ t,
                                                      __bf16* __restrict__ y, int B, int n, int D, float eps,
-                                                     const int* __restrict__ len, const float* __restrict__ part,
-                                                     int K) {
+                                                     const int* __restrict__ len, const int* __restrict__ xidx,
+                                                     const float* __restrict__ part, int K) {
   extern __shared__ int pre[];
   pack_prefix(pre, len, B, n);
   __syncthreads();
@@ -500,7 +503,9 @@ __global__ __launch_bounds__(256) void k_residual_ln(const __bf16* __restrict__ 
   const GemmPlan pl = gemm_plan(R, D / kBN, K / kGK, part != nullptr);
   for (int p = blockIdx.x * 4 + (threadIdx.x >> 6); p < R; p += gridDim.x * 4) {
     const int b = pack_seq(pre, B, p);
-    ln_row<kMaxPer>(xr, t, y, D, eps, part, pl, (long long)b * n + (p - pre[b]), p, lane);
+    const long long row = (long long)b * n + (p - pre[b]);
+    const long long xrow = xidx ? (long long)b * n + clampi(xidx[row], 0, n - 1) : row;
+    ln_row<kMaxPer>(xr, t, y, D, eps, part, pl, row, xrow, p, lane);
   }
 }
 
@@ -517,7 +522,7 @@ bool gemm_v3_ok(int B, int n, int K, int N) {
 }  // namespace
 
 hipError_t launch_gemm_bf16(const void* x, const void* w, void* y, int mode, int B, int n, int K, int N,
-                            const int* len, float* part, hipStream_t s) {
+                            const int* len, const int* xidx, float* part, hipStream_t s) {
   if (gemm_v3_ok(B, n, K, N)) {
     // items: at most ceil(B n / 128) 128-row tiles x N tiles, kSplitBlocks for
     // a split, kOneRound for 64-row tiles
@@ -528,21 +533,21 @@ hipError_t launch_gemm_bf16(const void* x, const void* w, void* y, int mode, int
     const __bf16* xb = static_cast<const __bf16*>(x);
     const __bf16* wb = static_cast<const __bf16*>(w);
     if (mode == kGemmF32)
-      hipLaunchKernelGGL(k_gemm_v3<kGemmF32>, grid, block, 0, s, xb, wb, y, B, n, K, N, len, part);
+      hipLaunchKernelGGL(k_gemm_v3<kGemmF32>, grid, block, 0, s, xb, wb, y, B, n, K, N, len, xidx, part);
     else if (mode == kGemmGeluBf16)
-      hipLaunchKernelGGL(k_gemm_v3<kGemmGeluBf16>, grid, block, 0, s, xb, wb, y, B, n, K, N, len, nullptr);
+      hipLaunchKernelGGL(k_gemm_v3<kGemmGeluBf16>, grid, block, 0, s, xb, wb, y, B, n, K, N, len, xidx, nullptr);
     else
-      hipLaunchKernelGGL(k_gemm_v3<kGemmBf16>, grid, block, 0, s, xb, wb, y, B, n, K, N, len, nullptr);
+      hipLaunchKernelGGL(k_gemm_v3<kGemmBf16>, grid, block, 0, s, xb, wb, y, B, n, K, N, len, xidx, nullptr);
     return hipGetLastError();
   }
   dim3 grid((N + kBN - 1) / kBN, (n + kBM - 1) / kBM, B);
   hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, s, static_cast<const __bf16*>(x),
-                     static_cast<const __bf16*>(w), y, mode, n, K, N, len);
+                     static_cast<const __bf16*>(w), y, mode, n, K, N, len, xidx);
   return hipGetLastError();
 }
 
 hipError_t launch_residual_layernorm(const void* x_res, const float* t, void* y, int B, int n, int D, float eps,
-                                     const int* len, const float* part, int K, hipStream_t s) {
+                                     const int* len, const int* xidx, const float* part, int K, hipStream_t s) {
   const long long rows = (long long)B * n;
   if (!gemm_v3_ok(B, n, K, D)) part = nullptr;  // the product took the path without a split
   auto* kern = D <= 1024 ? k_residual_ln<16> : k_residual_ln<32>;  // D <= 2048 (checked by the caller)
@@ -552,7 +557,7 @@ hipError_t launch_residual_layernorm(const void* x_res, const float* t, void* y,
   // table: 7.5 -> 6.3 us in the stack's late layers)
   const long long blocks = std::min<long long>((rows + 3) / 4, 1024);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), sizeof(int) * (B + 1), s,
-                     static_cast<const __bf16*>(x_res), t, static_cast<__bf16*>(y), B, n, D, eps, len, part, K);
+                     static_cast<const __bf16*>(x_res), t, static_cast<__bf16*>(y), B, n, D, eps, len, xidx, part, K);
   return hipGetLastError();
 }
 
