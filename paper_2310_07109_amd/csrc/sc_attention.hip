@@ -2449,8 +2449,9 @@ constexpr int kSpanOrderMaxN = 4096;
 // 128 queries (H12): B8 n4096 window 512 with 32 slots 92.5 and 83.6, causal
 // 74.2 and 65.6, B2 H16 n8192 window 1024 with 64 slots 118.7 and 110.3, B1
 // n4096 24.4 and 24.4; but B1 n2048 17.9 and 19.8, B1 n1024 window 256 12.5
-// and 15.4 (B64 n1024 80.7 and 75.2).
-constexpr int kWideMinN = 3072;
+// and 15.4 (B64 n1024 80.7 and 75.2), and the layer step of B1 n3749 causal
+// window 842 51.4 and 52.7.
+constexpr int kWideMinN = 4096;
 
 template <int DT>
 static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {

@@ -79,6 +79,14 @@ SC_DEV i16x4 lds_read_tr16(const void* p) {
       (__attribute__((address_space(3))) i16x4*)(const_cast<void*>(p)));
 }
 
+// 16-byte and transposing 8-byte reads at an LDS byte address.
+SC_DEV bf16x8 lds_read16(unsigned addr) {
+  return *(const __attribute__((address_space(3))) bf16x8*)(size_t)addr;
+}
+SC_DEV i16x4 lds_read_tr16(unsigned addr) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(size_t)addr);
+}
+
 // The lane id, opaque to the compiler: values derived from it are
 // recomputed where they are used instead of being hoisted out of the tile
 // loops and held in registers across them.

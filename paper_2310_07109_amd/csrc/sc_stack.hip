@@ -36,6 +36,8 @@
 //               sums into slabs; the residual LayerNorm adds the slabs in the
 //               fixed order s = 0 .. S-1.  Both kernels derive the packing and
 //               S from the lengths, so the host needs no synchronisation.
+// k_gemm_v4     the same product for calls of few rows (kV4Rows), laid out for
+//               latency: see below.
 // k_residual_ln y = bf16(LayerNorm(x + t)), one wavefront per packed row, fp32
 //               statistics (biased variance), gamma = 1, beta = 0.
 #include <algorithm>
@@ -408,6 +410,260 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     gemm_tile<64, 4, kMode>(X, W, Y, stage, grow, xrow, K, N, nt * kBN, s0, s1, nullptr);
 }
 
+// ---------------------------------------------------------------------------
+// k_gemm_v4: the packed product for calls of at most kV4Rows rows.  Few rows
+// make few tiles, and a tile's time is then the round trips of its loads, a
+// microsecond or more each (the weights come from beyond the L2): k_gemm_v3
+// keeps 36 KB of stages in flight per workgroup.  Here one workgroup of 512
+// threads has a CU's LDS to itself, 144 KB of stage buffers all but one in
+// flight, K stages of 64 (whole 128-byte rows of X), and tiles down to 64 x 64
+// put more CUs to work.  One file of 512 tokens, D 768, FFN 3072, us per launch
+// before -> after: QKV 15.0 -> 12.0, W1 16.3 -> 12.7, and with 64 rows left 14.2 ->
+// 9.3 and 15.4 -> 8.8.
+struct Plan4 {
+  int mode, bm, T, Nt, S;
+};
+constexpr int kModes4 = 3;
+constexpr int kBm4[kModes4] = {128, 64, 64}, kBn4[kModes4] = {128, 128, 64};
+constexpr int kGK4 = 64;
+constexpr int kStage4 = 147456;  // stage buffers: 4 x 32 KB, 6 x 24 KB or 9 x 16 KB
+constexpr int kMaxB4 = 2048;     // sequences whose prefix table fits beside them
+constexpr int kWgs4 = 256;       // one workgroup per CU, each taking items in turn
+// Rows (B n) up to which k_gemm_v4 takes the product.  A 12-layer encoder's layer
+// with every row kept, D 768, FFN 3072, us with k_gemm_v3 and v4: 512 rows
+// 90.7 and 82.7, 1024 107 and 93, 2048 131 and 121, 4096 166 and 162; 6144 218
+// and 237 (larger tiles of this kernel, 256 x 128 and 256 x 256, did not beat
+// k_gemm_v3's three workgroups per CU: 572 against 620 at 24 576 rows).
+constexpr int kV4Rows = 4096;
+// Microseconds of a K stage per mode, and of an item beside its stages,
+// fitted to measured launches; the plan takes the cheapest mode and split by
+// rounds x (stages x stage + 2).  Splits (float32 outputs with slabs) as in
+// k_gemm_v3: S workgroups take K / S each, the LayerNorm adds the slabs, which
+// costs it about 0.1 us per 1024 rows of slab.
+SC_DEV float stage_us4(int m) { return m == 0 ? 0.33f : m == 1 ? 0.21f : 0.15f; }
+SC_DEV Plan4 gemm_plan4(int R, int N, int nk, bool split) {
+  // lane 4 m + s prices mode m with S = 2^s; the cheapest wins (ties: the lower lane)
+  const int lane = threadIdx.x & 63, m = (lane >> 2) & 3, S = 1 << (lane & 3);
+  const int bm = m == 0 ? 128 : 64, bn = m == 2 ? 64 : 128;
+  const int T = (R + bm - 1) / bm, per = nk >> (lane & 3);
+  bool ok = m < kModes4 && (N & (bn - 1)) == 0 && per >= 2 && per << (lane & 3) == nk;
+  ok = ok && (S == 1 || split);
+  ok = ok && (S == 1 || (long long)T * bm * S <= kGemmSplitRows);
+  const int rounds = (T * (N / bn) * S + kWgs4 - 1) / kWgs4;
+  float t = rounds * (per * stage_us4(m) + 2.0f) + (S > 1 ? 0.4f * S * T * bm / 4096.f : 0.f);
+  if (!ok) t = 1e30f;
+  int best = lane & 15;
+#pragma unroll
+  for (int d = 1; d < 16; d <<= 1) {
+    const float to = __shfl_xor(t, d, 64);
+    const int bo = __shfl_xor(best, d, 64);
+    const bool take = to < t || (to == t && bo < best);
+    t = take ? to : t;
+    best = take ? bo : best;
+  }
+  best = __builtin_amdgcn_readfirstlane(best);
+  Plan4 p;
+  p.mode = best >> 2;
+  p.bm = p.mode == 0 ? 128 : 64;
+  p.T = (R + p.bm - 1) / p.bm;
+  p.Nt = N / (p.mode == 2 ? 64 : 128);
+  p.S = 1 << (best & 3);
+  return p;
+}
+
+// Row tables of packed tile t: the rows of Y it writes (-1: past the packed
+// ones) and of X it reads (the last packed row past them).
+SC_DEV void tile_rows4(int* grow, int* xrow, const int* pre, const int* xidx, int B, int n, int R, int m0, int bm) {
+  if ((int)threadIdx.x >= bm) return;
+  const int q = m0 + threadIdx.x, p = min(q, R - 1);
+  const int b = pack_seq(pre, B, p);
+  const int gr = b * n + (p - pre[b]);
+  grow[threadIdx.x] = q < R ? gr : -1;
+  xrow[threadIdx.x] = xidx ? b * n + clampi(xidx[gr], 0, n - 1) : gr;
+}
+
+// Waits until at most `later` (< kNBuf) stages of kPer loads are in flight.
+template <int kNBuf, int kPer, int kL = kNBuf - 1>
+SC_DEV void wait_stages(int later) {
+  if constexpr (kL == 0) {
+    wait_vm<0>();
+  } else {
+    if (later >= kL) wait_vm<kL * kPer>();
+    else wait_stages<kNBuf, kPer, kL - 1>(later);
+  }
+}
+
+template <int kM, int kMode>
+SC_DEV void gemm_run4(const __bf16* __restrict__ X, const __bf16* __restrict__ W, void* __restrict__ Y, char* stage,
+                      int* rows, const int* pre, const int* __restrict__ xidx, int B, int n, int R, int K, int N,
+                      const Plan4& pl, float* part) {
+  constexpr int BM = kBm4[kM], BN = kBn4[kM];
+  constexpr int WGM = kM == 2 ? 4 : 2, WGN = 8 / WGM;  // waves along M and N
+  constexpr int WM = BM / WGM, WN = BN / WGN, FI = WM / 16, FJ = WN / 16;
+  constexpr int XL = BM / 64, WL = BN / 64;  // loads per wave and stage
+  constexpr int kPer = XL + WL;
+  constexpr int kXB = BM * kGK4 * 2, kWB = kGK4 * BN * 2;
+  constexpr int kNBuf = kStage4 / (kXB + kWB);
+  static_assert(kNBuf >= 2 && kNBuf <= 9, "stage buffers");
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4,
+            lr = lane & 15;
+  const int wm = (w / WGN) * WM, wn = (w % WGN) * WN;
+  const int nk = K / kGK4, per = __builtin_amdgcn_readfirstlane(nk / pl.S);
+  const int items = pl.T * pl.Nt * pl.S;
+  const int xcd = blockIdx.x & 7, hi = (int)((long long)items * (xcd + 1) / 8);
+  const int step = gridDim.x >> 3;
+  int item = (int)((long long)items * xcd / 8) + (blockIdx.x >> 3);
+  if (item >= hi) return;
+  // this lane's W offset per load (stage k0 = 0, n0 = 0)
+  constexpr int kUr = BN / 8, kRi = 64 / kUr;  // units per W row, rows per load
+  constexpr int kWx = BN == 64 ? 1 : 2;        // W rows swizzle by kWx times their low 3 bits
+  unsigned woff[WL];
+#pragma unroll
+  for (int t = 0; t < WL; ++t) {
+    const int r = 8 * w + kRi * t + lane / kUr;
+    woff[t] = (unsigned)gw_krow(r) * 2u * (unsigned)N + 16u * ((lane % kUr) ^ (kWx * (r & 7)));
+  }
+  unsigned xoff[XL];
+  int n0 = 0, s0 = 0, cur = 0;
+  const unsigned lds0 = lds_addr(stage);
+  auto setup = [&](int it, int buf) {  // tables and offsets of an item (its tables' barrier included)
+    const int ks = it % pl.S, nt = it / pl.S % pl.Nt, t = it / pl.S / pl.Nt;
+    int* grow = rows + 512 * buf;
+    tile_rows4(grow, grow + 256, pre, xidx, B, n, R, __builtin_amdgcn_readfirstlane(t * BM), BM);
+    n0 = __builtin_amdgcn_readfirstlane(nt * BN);
+    s0 = __builtin_amdgcn_readfirstlane(ks * per);
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < XL; ++x)
+      xoff[x] = (unsigned)grow[256 + (BM / 8) * w + 8 * x + (lane >> 3)] * 2u * (unsigned)K +
+                16u * ((lane & 7) ^ (lane >> 3));
+  };
+  auto issue = [&](int s, int bf) {  // stage s of the item into buffer bf
+    const __bf16* xb = X + (size_t)(s0 + s) * kGK4;
+    const __bf16* wb = W + (size_t)(s0 + s) * kGK4 * N + n0;
+    const unsigned lx = lds0 + (unsigned)bf * (kXB + kWB), lw = lx + kXB;
+#pragma unroll
+    for (int x = 0; x < XL; ++x) lds_dma16(xb, xoff[x], lx + ((BM / 8) * w + 8 * x) * 128u);
+#pragma unroll
+    for (int t = 0; t < WL; ++t) lds_dma16(wb, woff[t], lw + (8 * w + kRi * t) * (2u * BN));
+  };
+  // LDS addresses of the lane's fragments in buffer 0: A (unit of k-chunk kc:
+  // xor 64 kc), B (row chunk kc: + 32 rows)
+  const unsigned aa = lds0 + (wm + lr) * 128u + 16u * (g ^ (lr & 7));
+  const int vr = 4 * g + (lr >> 2);
+  unsigned ba[FJ];
+#pragma unroll
+  for (int j = 0; j < FJ; ++j)
+    ba[j] = lds0 + kXB + vr * (2u * BN) + 16u * ((2 * ((wn >> 4) + j) + ((lr >> 1) & 1)) ^ (kWx * (vr & 7))) + 8u * (lr & 1);
+  bf16x8 af[2][FI], bq[2][FJ];  // fragments of the two k-chunks of 32
+  auto frags = [&](unsigned ob, int kc) {
+#pragma unroll
+    for (int j = 0; j < FJ; ++j) {
+      const i16x4 a0 = lds_read_tr16(ba[j] + ob + 32u * kc * (2u * BN));
+      const i16x4 a1 = lds_read_tr16(ba[j] + ob + (32u * kc + 16u) * (2u * BN));
+      bq[kc][j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+#pragma unroll
+    for (int i = 0; i < FI; ++i) af[kc][i] = lds_read16((aa ^ (64u * kc)) + ob + i * 2048u);
+  };
+  setup(item, cur);
+#pragma unroll
+  for (int p = 0; p < kNBuf; ++p)
+    if (p < per) issue(p, p);
+  wait_stages<kNBuf, kPer>(min(per, kNBuf) - 1);
+  while (true) {
+    f32x4 acc[FI][FJ];
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < FJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](int kc) {
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+#pragma unroll
+        for (int j = 0; j < FJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[kc][j], af[kc][i], acc[i][j], 0, 0, 0);
+    };
+    // One barrier per stage, between its two k-chunks: the second chunk's
+    // fragments are in flight during the first chunk's products, the next
+    // stage's first ones during the second's, and a stage's buffer is
+    // refilled as soon as every wave has read it.
+    __syncthreads();
+    int bf = 0;
+    frags(0u, 0);
+    for (int s = 0; s < per; ++s) {
+      const int bn = bf == kNBuf - 1 ? 0 : bf + 1;
+      frags((unsigned)bf * (kXB + kWB), 1);
+      mul(0);
+      if (s + 1 < per) {
+        wait_stages<kNBuf, kPer>(min(per - 2 - s, kNBuf - 2));
+        __syncthreads();
+        if (s + kNBuf < per) issue(s + kNBuf, bf);
+        frags((unsigned)bn * (kXB + kWB), 0);
+      }
+      mul(1);
+      bf = bn;
+    }
+    // the next item's first stages load while this item's results are stored
+    const int on0 = n0, ot = item / pl.S / pl.Nt, oks = item % pl.S, ocur = cur;
+    item += step;
+    const bool more = item < hi;
+    __syncthreads();  // every wave has read the last stage
+    if (more) {
+      cur ^= 1;
+      setup(item, cur);
+#pragma unroll
+      for (int p = 0; p < kNBuf; ++p)
+        if (p < per) issue(p, p);
+    }
+    const int* grow = rows + 512 * ocur;
+    float* slab = pl.S > 1 ? part + ((size_t)oks * pl.T * BM + (size_t)ot * BM) * N : nullptr;
+#pragma unroll
+    for (int i = 0; i < FI; ++i) {
+      const int r = wm + 16 * i + lr, gr = grow[r];
+      if (gr >= 0) {
+        const int col = on0 + wn + 4 * g;
+#pragma unroll
+        for (int j = 0; j < FJ; ++j) {
+          if constexpr (kMode == kGemmF32) {
+            float* d = slab ? slab + (size_t)r * N : static_cast<float*>(Y) + (size_t)gr * N;
+            *reinterpret_cast<f32x4*>(d + col + 16 * j) = acc[i][j];
+          } else {
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              v[e] = (__bf16)(kMode == kGemmGeluBf16 ? gelu_exact(acc[i][j][e]) : acc[i][j][e]);
+            *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(Y) + (size_t)gr * N + col + 16 * j) = v;
+          }
+        }
+      }
+    }
+    if (!more) break;
+    wait_vm<0>();  // the next item's first stages, and the stores, which share the counter
+  }
+}
+
+template <int kMode>
+__global__ __launch_bounds__(512) void k_gemm_v4(const __bf16* __restrict__ X, const __bf16* __restrict__ W,
+                                                 void* __restrict__ Y, int B, int n, int K, int N,
+                                                 const int* __restrict__ len, const int* __restrict__ xidx,
+                                                 float* __restrict__ part) {
+  extern __shared__ __attribute__((aligned(1024))) char sm4[];  // stages, two row tables, prefix table
+  int* rows = reinterpret_cast<int*>(sm4 + kStage4);
+  int* pre = rows + 1024;
+  pack_prefix(pre, len, B, n);
+  __syncthreads();
+  const int R = __builtin_amdgcn_readfirstlane(pre[B]);
+  if (R == 0) return;
+  const Plan4 pl = gemm_plan4(R, N, K / kGK4, kMode == kGemmF32 && part != nullptr);
+  if (pl.mode == 0)
+    gemm_run4<0, kMode>(X, W, Y, sm4, rows, pre, xidx, B, n, R, K, N, pl, part);
+  else if (pl.mode == 1)
+    gemm_run4<1, kMode>(X, W, Y, sm4, rows, pre, xidx, B, n, R, K, N, pl, part);
+  else
+    gemm_run4<2, kMode>(X, W, Y, sm4, rows, pre, xidx, B, n, R, K, N, pl, part);
+}
+
 // v[4u + q] = x[c + q] + t[c + q] for the columns c = 4 lane + 256 u .. +3
 // (D a multiple of 64), t being the sum of S partial sums that lie `stride`
 // floats apart, added in the order s = 0 .. S-1; 16-byte loads of t.
@@ -443,19 +699,19 @@ SC_DEV void ln_load(float (&v)[kPer], const __bf16* xp, const float* tp, long lo
 // being row xrow of xr.
 template <int kMaxPer>
 SC_DEV void ln_row(const __bf16* __restrict__ xr, const float* __restrict__ t, __bf16* __restrict__ y, int D,
-                   float eps, const float* __restrict__ part, const GemmPlan& pl, long long row, long long xrow, int p,
-                   int lane) {
+                   float eps, const float* __restrict__ part, int S, long long srows, long long row, long long xrow,
+                   int p, int lane) {
   const __bf16* xp = xr + xrow * D;
   __bf16* yp = y + row * D;
   float v[kMaxPer];
-  if (pl.S == 1) {
+  if (S == 1) {
     ln_load<1, kMaxPer>(v, xp, t + row * D, 0, D, lane);
   } else {  // the row's partial sums sit at its packed index in each slab
     const float* tp = part + (long long)p * D;
-    const long long stride = (long long)pl.T * 128 * D;
-    if (pl.S == 2)
+    const long long stride = srows * D;
+    if (S == 2)
       ln_load<2, kMaxPer>(v, xp, tp, stride, D, lane);
-    else if (pl.S == 4)
+    else if (S == 4)
       ln_load<4, kMaxPer>(v, xp, tp, stride, D, lane);
     else
       ln_load<8, kMaxPer>(v, xp, tp, stride, D, lane);
@@ -494,18 +750,28 @@ template <int kMaxPer>
 __global__ __launch_bounds__(256) void k_residual_ln(const __bf16* __restrict__ xr, const float* __restrict__ t,
                                                      __bf16* __restrict__ y, int B, int n, int D, float eps,
                                                      const int* __restrict__ len, const int* __restrict__ xidx,
-                                                     const float* __restrict__ part, int K) {
+                                                     const float* __restrict__ part, int K, int v4) {
   extern __shared__ int pre[];
   pack_prefix(pre, len, B, n);
   __syncthreads();
   const int R = pre[B];
   const int lane = threadIdx.x & 63;
-  const GemmPlan pl = gemm_plan(R, D / kBN, K / kGK, part != nullptr);
+  // ranges of the product's split, and rows per slab
+  int S = 1, srows = 0;
+  if (v4) {
+    const Plan4 pl = gemm_plan4(max(R, 1), D, K / kGK4, part != nullptr);
+    S = pl.S;
+    srows = pl.T * pl.bm;
+  } else {
+    const GemmPlan pl = gemm_plan(R, D / kBN, K / kGK, part != nullptr);
+    S = pl.S;
+    srows = pl.T * 128;
+  }
   for (int p = blockIdx.x * 4 + (threadIdx.x >> 6); p < R; p += gridDim.x * 4) {
     const int b = pack_seq(pre, B, p);
     const long long row = (long long)b * n + (p - pre[b]);
     const long long xrow = xidx ? (long long)b * n + clampi(xidx[row], 0, n - 1) : row;
-    ln_row<kMaxPer>(xr, t, y, D, eps, part, pl, row, xrow, p, lane);
+    ln_row<kMaxPer>(xr, t, y, D, eps, part, S, srows, row, xrow, p, lane);
   }
 }
 
@@ -521,8 +787,33 @@ bool gemm_v3_ok(int B, int n, int K, int N) {
 }
 }  // namespace
 
+// Shapes of k_gemm_v4: as k_gemm_v3 with K whole stages of 64 (two at least),
+// few rows, and a batch whose prefix table fits beside the stage buffers.
+static bool gemm_v4_ok(int B, int n, int K, int N) {
+  return gemm_v3_ok(B, n, K, N) && K % kGK4 == 0 && K >= 2 * kGK4 && B <= kMaxB4 && (long long)B * n <= kV4Rows;
+}
+
+template <int kMode>
+static hipError_t launch_v4(const __bf16* x, const __bf16* w, void* y, int B, int n, int K, int N, const int* len,
+                            const int* xidx, float* part, hipStream_t s) {
+  constexpr int kLds = kStage4 + 4096 + 4 * (kMaxB4 + 4);
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_v4<kMode>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return attr;
+  const int lds = kStage4 + 4096 + 4 * (B + 4);
+  hipLaunchKernelGGL(k_gemm_v4<kMode>, dim3(kWgs4), dim3(512), lds, s, x, w, y, B, n, K, N, len, xidx, part);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_bf16(const void* x, const void* w, void* y, int mode, int B, int n, int K, int N,
                             const int* len, const int* xidx, float* part, hipStream_t s) {
+  if (gemm_v4_ok(B, n, K, N)) {
+    const __bf16* xb = static_cast<const __bf16*>(x);
+    const __bf16* wb = static_cast<const __bf16*>(w);
+    if (mode == kGemmF32) return launch_v4<kGemmF32>(xb, wb, y, B, n, K, N, len, xidx, part, s);
+    if (mode == kGemmGeluBf16) return launch_v4<kGemmGeluBf16>(xb, wb, y, B, n, K, N, len, xidx, nullptr, s);
+    return launch_v4<kGemmBf16>(xb, wb, y, B, n, K, N, len, xidx, nullptr, s);
+  }
   if (gemm_v3_ok(B, n, K, N)) {
     // items: at most ceil(B n / 128) 128-row tiles x N tiles, kSplitBlocks for
     // a split, kOneRound for 64-row tiles
@@ -557,7 +848,7 @@ hipError_t launch_residual_layernorm(const void* x_res, const float* t, void* y,
   // table: 7.5 -> 6.3 us in the stack's late layers)
   const long long blocks = std::min<long long>((rows + 3) / 4, 1024);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), sizeof(int) * (B + 1), s,
-                     static_cast<const __bf16*>(x_res), t, static_cast<__bf16*>(y), B, n, D, eps, len, xidx, part, K);
+                     static_cast<const __bf16*>(x_res), t, static_cast<__bf16*>(y), B, n, D, eps, len, xidx, part, K, gemm_v4_ok(B, n, K, D) ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -417,17 +417,17 @@ def test_dispatch_order_invariance(causal):
 
 
 @pytest.mark.parametrize("n,lens,window,G,causal", [
-    (3072, (3072, 1, 129, 33), 33, 3, 0),        # odd window; a sequence of one token, one query in a second block
-    (3073, (3073, 0, 128, 97), 16, 70, 0),       # one query in the last block; two 64-slot tiles; an empty sequence
-    (3100, (3100, 300, 65, 31), 64, 33, 0),      # 33 slots: one in the second half of a tile; band edges on halves
-    (3072, (1000, 257, 130, 64), 0, 130, 0),     # window 0; three 64-slot tiles
-    (3075, (260, 700, 2, 500), 2000, 64, 0),     # the window covers the sequences: no key outside a band
-    (3072, (3071, 1500, 700, 160), 400, 5, 0),   # interior tiles between the edges
-    (3100, (3100, 300, 130, 1), 64, 70, 1),
-    (3072, (2999, 257, 96, 0), 33, 0, 1),
+    (4096, (4096, 1, 129, 33), 33, 3, 0),        # odd window; a sequence of one token, one query in a second block
+    (4097, (4097, 0, 128, 97), 16, 70, 0),       # one query in the last block; two 64-slot tiles; an empty sequence
+    (4124, (4124, 300, 65, 31), 64, 33, 0),      # 33 slots: one in the second half of a tile; band edges on halves
+    (4096, (1000, 257, 130, 64), 0, 130, 0),     # window 0; three 64-slot tiles
+    (4099, (260, 700, 2, 500), 2000, 64, 0),     # the window covers the sequences: no key outside a band
+    (4096, (4095, 1500, 700, 160), 400, 5, 0),   # interior tiles between the edges
+    (4124, (4124, 300, 130, 1), 64, 70, 1),
+    (4096, (2999, 257, 96, 0), 33, 0, 1),
 ])
 def test_wide_query_blocks(n, lens, window, G, causal):
-    """The 128-query window blocks (sequences padded to 3072 tokens or more): lengths at their edges, band edges
+    """The 128-query window blocks (sequences padded to 4096 tokens or more): lengths at their edges, band edges
     inside and between the 32-key halves, global keys inside and outside the bands.  Logits of order one (inputs
     N(0, 1)), so that a key too many or too few moves the LSE beyond its tolerance."""
     cfg = si.AttnConfig("wide", 31, 4, n, 2, 64, "bf16", window, (n, n), G, "random", input_scale=1.0)

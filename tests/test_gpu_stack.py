@@ -242,3 +242,31 @@ def test_split_reduction_full_layers():
     assert np.array_equal(fl2.cpu().numpy(), fl) and torch.equal(orig2, orig) and torch.equal(kpl2, kpl)
     for b in range(cfg.B):
         assert torch.equal(y2[b, :fl[b]].view(torch.int16), y[b, :fl[b]].view(torch.int16))
+
+
+@pytest.mark.parametrize("H,F,lens", [
+    (2, 128, (1,)),                      # one row; products of two K stages
+    (2, 384, (63, 1, 0, 65)),            # 129 rows: one past two 64-row tiles; six K stages
+    (4, 512, (64, 64)),                  # whole tiles
+    (4, 192, (200, 130, 3)),             # N = 192: not a multiple of 128, the unpacked product
+    (12, 3072, (33, 31)),                # RoBERTa widths on one tile: the widest split
+    (12, 3072, (700, 650, 640)),         # several items per workgroup
+    (6, 768, (1024, 1023, 1000, 1025)),  # more than 4096 padded rows: the three-workgroup product
+])
+def test_products_of_few_rows(H, F, lens):
+    """One unpruned full layer at the edges of the small products' tiles, splits and row limit."""
+    B, n = len(lens), max(lens)
+    cfg = si.StackConfig("rows", 41, B, n, H, 64, 1, 32, (n, n), 1, 0.04, 0.0, ffn_dim=F, windows=(32,))
+    inp = si.make_stack_inputs(cfg)
+    vl = np.array(lens, np.int32)
+    gp = si.global_positions(41, vl, 1, "first")
+    d = sc.Desc(B, n, H, 32, dev_i32(vl), dev_i32(gp), cfg.alpha, sc.SC_BF16)
+    dv = lambda ws: [bf16_dev(w) for w in ws]  # noqa: E731
+    y, fl, _, _ = sc.sc_encoder_stack(d, bf16_dev(inp["x"]), dv(inp["wqkv"]), dv(inp["wo"]), dv(inp["w1"]),
+                                      dv(inp["w2"]), [-1.0], windows=[32])
+    assert np.array_equal(fl.cpu().numpy(), vl)
+    ry, _, _, _ = oracle.encoder_stack(inp["x64"], inp["wqkv64"], inp["wo64"], vl, gp, H, [32], cfg.alpha, [-1.0],
+                                       w1_list=inp["w1_64"], w2_list=inp["w2_64"])
+    yy = to_f64(y, vl)
+    for b, L in enumerate(lens):
+        check_out(yy[b, :L], ry[b, :L], "bf16", what=f"sequence {b}", bf16_step=True)
