@@ -500,7 +500,7 @@ sc::SoftArgs soft_args(const sc_attn_desc* d) {
   a.valid_len = d->valid_len;
   a.gpos = d->G > 0 ? d->global_pos : nullptr;
   a.alpha = d->softmax_scale;
-  a.c2 = d->softmax_scale * 1.4426950408889634f;
+  a.c2 = std::max(d->softmax_scale * 1.4426950408889634f, FLT_MIN);  // positive: keeps excluded logits at -inf
   return a;
 }
 

@@ -288,16 +288,17 @@ SC_DEV void bwd_rows(const SoftArgs& a, int blk, Smem& sm, uint32_t* sBits) {
         }
       return;
     }
-    build_bits(sBits, gp, G, L, n);
   } else {
     if (span * kBwdSpan >= L) return;
   }
-  // this lane's query
+  // this lane's query; its rows are loaded before the block knows which of
+  // its queries are global (those lanes compute values that are never stored),
+  // so that the positions, the first tile and the rows arrive together
   int q, slot = 0;
   bool qok;
   if constexpr (!kGRows) {
     q = q0 + 16 * w + lr;
-    qok = q < L && !bit_of(sBits, q);
+    qok = q < L;
   } else {
     slot = 64 * gc + 16 * w + lr;
     q = (gp && slot < G) ? gp[slot] : -1;
@@ -355,6 +356,11 @@ SC_DEV void bwd_rows(const SoftArgs& a, int blk, Smem& sm, uint32_t* sBits) {
       if constexpr (kMode == 1) lds_dma16(a.v + seq, voff, lds_addr(&sm.sV[buf][R0 * TRb::kPitch]));
     }
   };
+  if (nt > 0) issue(0, 0);
+  if constexpr (!kGRows) {
+    build_bits(sBits, gp, G, L, n);
+    qok = qok && !bit_of(sBits, q);
+  }
   float pg = 0.f;
   f32x4 acc[4];
 #pragma unroll
@@ -366,15 +372,18 @@ SC_DEV void bwd_rows(const SoftArgs& a, int blk, Smem& sm, uint32_t* sBits) {
   auto tile = [&](auto edge_c, int t, int cur) {
     constexpr bool kEdge = decltype(edge_c)::value;
     const int kbase = kt0 + 64 * t;
-    f32x4 s[4];
-    mma_rows(sK[cur], qf, s, lr, g);
+    // the products accumulate onto the keys' bias: 0, or -inf (which the
+    // positive scale and the finite LSE keep)
+    f32x4 s[4], bias[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) bias[st] = *reinterpret_cast<const f32x4*>(&sBias[cur][16 * st + 4 * g]);
+    mma_rows(sK[cur], qf, s, lr, g, bias);
     float p[4][4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
-      const f32x4 bias = *reinterpret_cast<const f32x4*>(&sBias[cur][16 * st + 4 * g]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float x = fmaf(s[st][i], c2, -lse2) + bias[i];
+        float x = fmaf(s[st][i], c2, -lse2);
         if constexpr (kEdge) x = (unsigned)(kbase + 16 * st + 4 * g + i - q + r) <= (unsigned)(2 * r) ? x : -INFINITY;
         p[st][i] = fast_exp2(x);
       }
@@ -401,7 +410,6 @@ SC_DEV void bwd_rows(const SoftArgs& a, int blk, Smem& sm, uint32_t* sBits) {
     }
   };
   if (nt > 0) {
-    issue(0, 0);
     if (tid < 64) {
       const int key = key_of(0, tid);
       sBias[0][tid] = key >= 0 ? 0.f : -INFINITY;
@@ -518,15 +526,14 @@ SC_DEV void bwd_cols(const SoftArgs& a, int blk, ColSmem& sm, uint32_t* sBits) {
       }
       return;
     }
-    build_bits(sBits, gp, G, L, n);
   } else {
     if (span * kBwdSpan >= L) return;
   }
-  int k, slot = 0;
+  int k, slot = 0;  // as on the row side, the key's rows come before the positions
   bool kok;
   if constexpr (!kGCols) {
     k = k0 + 16 * w + lr;
-    kok = k < L && !bit_of(sBits, k);
+    kok = k < L;
   } else {
     slot = 64 * gc + 16 * w + lr;
     k = (gp && slot < G) ? gp[slot] : -1;
@@ -577,6 +584,11 @@ SC_DEV void bwd_cols(const SoftArgs& a, int blk, ColSmem& sm, uint32_t* sBits) {
       lds_dma16(a.dO + seq, voff, lds_addr(&sO[buf][R0 * TRb::kPitch]));
     }
   };
+  if (nt > 0) issue(0, 0);
+  if constexpr (!kGCols) {
+    build_bits(sBits, gp, G, L, n);
+    kok = kok && !bit_of(sBits, k);
+  }
   f32x4 accK[4], accV[4];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) {
@@ -611,7 +623,6 @@ SC_DEV void bwd_cols(const SoftArgs& a, int blk, ColSmem& sm, uint32_t* sBits) {
     mma_tr(sQ[cur], pS, accK);
   };
   if (nt > 0) {
-    issue(0, 0);
     if (tid < 64) {
       const int qq = query_of(0, tid);
       sL2[0][tid] = qq >= 0 ? a.lse[(long long)bh * n + qq] * kLog2e : INFINITY;

@@ -161,3 +161,14 @@ def test_soft_backward_deterministic():
     for key in ("mask", "y", "dq", "dk", "dv"):
         assert np.array_equal(a[key], b[key]), key
     assert a["dth"] == b["dth"]
+
+
+@pytest.mark.parametrize("keep_global", [0, 1])
+def test_soft_zero_scale(keep_global):
+    """Softmax scale 0 (uniform attention over the allowed keys): excluded keys stay excluded, and the scale that
+    multiplies dQ and dK makes them zero."""
+    cfg = si.AttnConfig("zero scale", 23, 2, 300, 2, 64, "bf16", 32, (200, 300), 3, "random", input_scale=1.0, alpha=0.0)
+    inp = si.make_attention_inputs(cfg)
+    gpu, ref = run_soft(inp, keep_global)
+    assert np.all(gpu["dq"] == 0.0) and np.all(gpu["dk"] == 0.0)
+    compare(gpu, ref, inp["valid_len"], f"soft zero scale {keep_global}")
