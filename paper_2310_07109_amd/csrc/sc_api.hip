@@ -238,7 +238,14 @@ sc_status window_attention(const sc_attn_desc* d, const void* q, const void* k, 
     a.bp_band = band_probs;
     a.bp_gcol = band_probs + (size_t)d->B * d->H * d->n * geo.bw;
     a.bp_grow = a.bp_gcol + (size_t)d->B * d->H * d->n * d->G;
-    if (sc::launch_fill_zero(band_probs, bp_b, s) != hipSuccess) return SC_EHIP;
+    // launch 2 writes the entries that are not zero; launch 1 clears the layout
+    // beside its own work when it is made of whole aligned 16-byte units
+    if (((reinterpret_cast<uintptr_t>(band_probs) | bp_b) & 15) == 0) {
+      a.fill = band_probs;
+      a.fill_units = (long long)(bp_b >> 4);
+    } else if (sc::launch_fill_zero(band_probs, bp_b, s) != hipSuccess) {
+      return SC_EHIP;
+    }
   }
   return sc::launch_window_attention(d->dtype, a, s) == hipSuccess ? SC_OK : SC_EHIP;
 }

@@ -1541,13 +1541,30 @@ __host__ __device__ inline FwdSpan fwd_span(const AttnArgs& a) {
 // Otherwise (longer sequences) the window blocks come first, pair by pair
 // (xcd_pair_map), and the global-row blocks last, where they fill the window
 // blocks' uneven tail.
-// BQ: queries per window block.
-template <int DT, int BQ>
-__global__ __launch_bounds__(kThreads) SC_OCC(DT == 1 ? 3 : 2) void k_attn_fwd(AttnArgs a) {
+// Zeroes 16-byte units [kFillUnits blk, kFillUnits (blk + 1)) of p.  As part of
+// launch 1 the clearing of the band layout, which is bound by memory, runs in
+// the gaps of the attention, which is bound by latency and VALU issue (a
+// launch of its own before it: 15 us for the 65 MB of B3 n1501 window 301).
+constexpr int kFillUnits = 4096;
+SC_DEV void fill_block(uint4* p, long long units, int blk) {
+  const long long u0 = (long long)kFillUnits * blk;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < kFillUnits; i += kThreads)
+    if (u0 + i < units) p[u0 + i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// BQ: queries per window block.  kFill: blocks from nfwd on zero a.fill.
+template <int DT, int BQ, bool kFill>
+__global__ __launch_bounds__(kThreads) SC_OCC(DT == 1 ? 3 : 2) void k_attn_fwd(AttnArgs a, int nfwd) {
   __shared__ Smem<DT> sm;
   extern __shared__ uint32_t sDyn[];
   constexpr int kSpanQB = kGlobalKeySpan / BQ;
   int bh, qb, gr = -1;  // a window block, or (gr >= 0) a global-row block
+  if constexpr (kFill)
+    if ((int)blockIdx.x >= nfwd) {  // the blocks past the attention's
+      fill_block(static_cast<uint4*>(a.fill), a.fill_units, blockIdx.x - nfwd);
+      return;
+    }
   if (a.span_major) {
     int c, o;
     xcd_span_map(blockIdx.x, a.nkc, fwd_span<BQ>(a).per, a.H * a.B, bh, c, o);
@@ -2471,14 +2488,20 @@ static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   // the spans' block counts (the host checks that they fit the grid limits)
   const int fwd_per = wide ? fwd_span<kBQ3>(a).per : fwd_span<kBQ>(a).per;
   const unsigned fwd_blocks = (unsigned)(a.span_major ? a.nkc * fwd_per * pairs : a.n_gr + a.nqb * pairs);
+  long long fill_blocks = a.fill ? (a.fill_units + kFillUnits - 1) / kFillUnits : 0;
+  if (fwd_blocks + fill_blocks >= (1LL << 31)) {  // past the grid limit: a launch of its own
+    const hipError_t e = launch_fill_zero(a.fill, (size_t)a.fill_units * 16, s);
+    if (e != hipSuccess) return e;
+    fill_blocks = 0;
+  }
   const int col_per = a.bp_band ? col_span<DT, true>(a).per : col_span<DT, false>(a).per;
   const unsigned col_blocks = (unsigned)(a.span_major ? a.nkc * col_per * pairs
                                                       : ((a.n_gr + 7) & ~7) + a.n_bcol + a.n_gcol);
   if (!a.no_profile) profile_mark(s, 0);
-  if (wide)
-    hipLaunchKernelGGL((k_attn_fwd<DT, DT == 1 ? kBQ3 : kBQ>), dim3(fwd_blocks), dim3(kThreads), dyn, s, a);
-  else
-    hipLaunchKernelGGL((k_attn_fwd<DT, kBQ>), dim3(fwd_blocks), dim3(kThreads), dyn, s, a);
+  constexpr int kBQW = DT == 1 ? kBQ3 : kBQ;
+  auto* fwd = fill_blocks > 0 ? (wide ? k_attn_fwd<DT, kBQW, true> : k_attn_fwd<DT, kBQ, true>)
+                              : (wide ? k_attn_fwd<DT, kBQW, false> : k_attn_fwd<DT, kBQ, false>);
+  hipLaunchKernelGGL(fwd, dim3((unsigned)(fwd_blocks + fill_blocks)), dim3(kThreads), dyn, s, a, (int)fwd_blocks);
   if (!a.no_profile) profile_mark(s, 1);
   if (col_blocks > 0) {
     if (a.bp_band)

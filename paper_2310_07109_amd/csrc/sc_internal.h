@@ -47,6 +47,8 @@ struct AttnArgs {
   float* bp_gcol;         // [B, H, n, G]
   float* bp_grow;         // [B, H, G, n]
   int bw, rb;             // bw = 2 * rb + 1
+  void* fill;             // memory that launch 1 zeroes for launch 2 (the band layout), or null
+  long long fill_units;   // its 16-byte units
 };
 
 struct AttnGeom {
