@@ -67,6 +67,39 @@ SC_DEV float xor32_max(float v) {
 SC_DEV float group_sum(float v) { return xor32_sum(xor16_sum(v)); }
 SC_DEV float group_max(float v) { return xor32_max(xor16_max(v)); }
 
+// Exchanges inside rows of 16 lanes on the VALU (DPP), a few cycles each where
+// __shfl goes through LDS.  kCtrl: quad_perm [1,0,3,2] and [2,3,0,1] are lane ^ 1
+// and lane ^ 2; the half-row and row mirrors stand for lane ^ 4 and lane ^ 8
+// once the lanes of a quad, then of a half row, hold the same value.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+template <int kCtrl>
+SC_DEV int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, true);
+}
+template <int kCtrl>
+SC_DEV float dpp(float v) {
+  return __builtin_bit_cast(float, dpp<kCtrl>(__builtin_bit_cast(int, v)));
+}
+// Sum over the 64 lanes, in every lane: the additions of an xor butterfly
+// (distances 1, 2, 4, 8, 16, 32), bit for bit.
+SC_DEV float butterfly_sum(float v) {
+  v += dpp<kDppXor1>(v);
+  v += dpp<kDppXor2>(v);
+  v += dpp<kDppHalfMirror>(v);
+  v += dpp<kDppMirror>(v);
+  return group_sum(v);
+}
+// Inclusive prefix sum over the 64 lanes.
+SC_DEV int prefix_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // lane 15 of rows 0, 2 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // lane 31 into rows 2 and 3
+  return v;
+}
+
 typedef __attribute__((ext_vector_type(4))) short i16x4;
 typedef __attribute__((ext_vector_type(8))) short i16x8;
 

@@ -168,14 +168,9 @@ SC_DEV void pack_prefix(int* pre, const int* len, int B, int n) {
   for (int c = 0; c < B; c += 64) {
     const int b = c + lane;
     const int v = b < B ? (len ? clampi(len[b], 0, n) : n) : 0;
-    int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += y;
-    }
+    const int incl = prefix_sum(v);
     if (b < B) pre[b] = carry + incl - v;
-    carry += __shfl(incl, 63, 64);
+    carry += __builtin_amdgcn_readlane(incl, 63);
   }
   if (lane == 0) pre[B] = carry;
 }
@@ -453,14 +448,15 @@ SC_DEV Plan4 gemm_plan4(int R, int N, int nk, bool split) {
   float t = rounds * (per * stage_us4(m) + 2.0f) + (S > 1 ? 0.4f * S * T * bm / 4096.f : 0.f);
   if (!ok) t = 1e30f;
   int best = lane & 15;
-#pragma unroll
-  for (int d = 1; d < 16; d <<= 1) {
-    const float to = __shfl_xor(t, d, 64);
-    const int bo = __shfl_xor(best, d, 64);
+  auto meet = [&](float to, int bo) {
     const bool take = to < t || (to == t && bo < best);
     t = take ? to : t;
     best = take ? bo : best;
-  }
+  };
+  meet(dpp<kDppXor1>(t), dpp<kDppXor1>(best));
+  meet(dpp<kDppXor2>(t), dpp<kDppXor2>(best));
+  meet(dpp<kDppHalfMirror>(t), dpp<kDppHalfMirror>(best));
+  meet(dpp<kDppMirror>(t), dpp<kDppMirror>(best));
   best = __builtin_amdgcn_readfirstlane(best);
   Plan4 p;
   p.mode = best >> 2;
@@ -719,7 +715,7 @@ SC_DEV void ln_row(const __bf16* __restrict__ xr, const float* __restrict__ t, _
   float s = 0.f;
 #pragma unroll
   for (int u = 0; u < kMaxPer; ++u) s += v[u];
-  for (int m = 1; m < 64; m <<= 1) s += __shfl_xor(s, m, 64);
+  s = butterfly_sum(s);
   const float mean = s / (float)D;
   float q = 0.f;
 #pragma unroll
@@ -728,7 +724,7 @@ SC_DEV void ln_row(const __bf16* __restrict__ xr, const float* __restrict__ t, _
     const float dv = c < D ? v[u] - mean : 0.f;
     q += dv * dv;
   }
-  for (int m = 1; m < 64; m <<= 1) q += __shfl_xor(q, m, 64);
+  q = butterfly_sum(q);
   const float inv = 1.0f / sqrtf(q / (float)D + eps);
 #pragma unroll
   for (int u = 0; u < kMaxPer / 4; ++u) {
