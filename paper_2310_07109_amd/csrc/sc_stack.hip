@@ -243,14 +243,17 @@ SC_DEV int gw_off(int row, int unit) { return row * kBN + 8 * (unit ^ (2 * (row 
 // 4g + t holds k = 8g + t and LDS row 16 + 4g + t holds k = 8g + 4 + t.
 SC_DEV int gw_krow(int r) { return (r & ~31) + 8 * ((r & 15) >> 2) + 4 * ((r >> 4) & 1) + (r & 3); }
 
+// Four consecutive columns (off a multiple of 4).
 template <int kMode>
-SC_DEV void gemm_store(void* Y, long long off, float v) {
-  if constexpr (kMode == kGemmF32)
-    static_cast<float*>(Y)[off] = v;
-  else if constexpr (kMode == kGemmGeluBf16)
-    static_cast<__bf16*>(Y)[off] = (__bf16)gelu_exact(v);
-  else
-    static_cast<__bf16*>(Y)[off] = (__bf16)v;
+SC_DEV void gemm_store4(void* Y, long long off, f32x4 v) {
+  if constexpr (kMode == kGemmF32) {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(Y) + off) = v;
+  } else {
+    bf16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(kMode == kGemmGeluBf16 ? gelu_exact(v[e]) : v[e]);
+    *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(Y) + off) = o;
+  }
 }
 
 // One output tile of BM x 128 (4 waves of BM/2 x 64, BM = 64, 128, 256) over this block's
@@ -339,25 +342,58 @@ SC_DEV void gemm_tile(const __bf16* __restrict__ X, const __bf16* __restrict__ W
     for (int i = 0; i < FI; ++i)
 #pragma unroll
       for (int jn = 0; jn < 4; ++jn)
-        acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[jn], acc[i][jn], 0, 0, 0);
+        acc[i][jn] = kMode == kGemmF32
+                         ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[jn], acc[i][jn], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[jn], af[i], acc[i][jn], 0, 0, 0);
   }
-  // result (tile row wm + 16i + 4g + e, col wn + 16jn + lr)
+  if constexpr (kMode == kGemmF32) {
+    // result (tile row wm + 16i + 4g + e, col wn + 16jn + lr): 64-byte runs of
+    // four rows per store.  (Staged through LDS like the bf16 results, W2 at
+    // 12 288 rows took 98 us instead of 88; four columns of 16 rows per store
+    // cost the whole layer 7 %.)
 #pragma unroll
-  for (int i = 0; i < FI; ++i)
+    for (int i = 0; i < FI; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = wm + 16 * i + 4 * g + e;
-      const int gr = grow[r];
-      if (gr < 0) continue;
-      const int col = n0 + wn + lr;
-      if (slab) {
+      for (int e = 0; e < 4; ++e) {
+        const int r = wm + 16 * i + 4 * g + e;
+        const int gr = grow[r];
+        if (gr < 0) continue;
+        float* d = (slab ? slab + (long long)r * N : static_cast<float*>(Y) + (long long)gr * N) + n0 + wn + lr;
 #pragma unroll
-        for (int jn = 0; jn < 4; ++jn) slab[(long long)r * N + col + 16 * jn] = acc[i][jn][e];
-      } else {
+        for (int jn = 0; jn < 4; ++jn) d[16 * jn] = acc[i][jn][e];
+      }
+  } else {
+    // W's fragment is the first operand, so that a lane holds four consecutive
+    // columns of a row (row wm + 16i + lr, cols wn + 16jn + 4g ..).  The wave's
+    // 64 columns go through its quarter of the stage buffers, kRows rows at a
+    // time (16-byte units swizzled by the row), and leave as whole 128-byte
+    // lines, 16 bytes a lane, instead of 2-byte stores of 32-byte runs: QKV at
+    // 24 576 rows, D 768, 104.9 -> 100.4 us, W1 149.4 -> 143.8.
+    constexpr int kRows = FI < 4 ? 32 : 64;
+    static_assert(kRows * 128 <= kStageBytes / 4 && (BM / 2) % kRows == 0, "staging rows");
+    char* st = stage + w * (kStageBytes / 4);
+    __syncthreads();  // every wave has read the last stage
 #pragma unroll
-        for (int jn = 0; jn < 4; ++jn) gemm_store<kMode>(Y, (long long)gr * N + col + 16 * jn, acc[i][jn][e]);
+    for (int c = 0; c < BM / 2 / kRows; ++c) {
+#pragma unroll
+      for (int i = 0; i < kRows / 16; ++i)
+#pragma unroll
+        for (int jn = 0; jn < 4; ++jn) {
+          const f32x4 v = acc[c * (kRows / 16) + i][jn];
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = (__bf16)(kMode == kGemmGeluBf16 ? gelu_exact(v[e]) : v[e]);
+          *reinterpret_cast<bf16x4*>(st + (16 * i + lr) * 128 + 16 * ((2 * jn + (g >> 1)) ^ (lr & 7)) + 8 * (g & 1)) = o;
+        }
+#pragma unroll
+      for (int x = 0; x < kRows / 8; ++x) {
+        const int row = 8 * x + (lane >> 3), gr = grow[wm + c * kRows + row];
+        const uint4 v = *reinterpret_cast<const uint4*>(st + row * 128 + 16 * ((lane ^ row) & 7));
+        if (gr < 0) continue;
+        *reinterpret_cast<uint4*>(static_cast<__bf16*>(Y) + (long long)gr * N + n0 + wn + 8 * (lane & 7)) = v;
       }
     }
+  }
 }
 
 // Y[row, N] = X[row, K] . W[K, N] over the surviving rows of the B
@@ -621,16 +657,10 @@ SC_DEV void gemm_run4(const __bf16* __restrict__ X, const __bf16* __restrict__ W
         const int col = on0 + wn + 4 * g;
 #pragma unroll
         for (int j = 0; j < FJ; ++j) {
-          if constexpr (kMode == kGemmF32) {
-            float* d = slab ? slab + (size_t)r * N : static_cast<float*>(Y) + (size_t)gr * N;
-            *reinterpret_cast<f32x4*>(d + col + 16 * j) = acc[i][j];
-          } else {
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              v[e] = (__bf16)(kMode == kGemmGeluBf16 ? gelu_exact(acc[i][j][e]) : acc[i][j][e]);
-            *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(Y) + (size_t)gr * N + col + 16 * j) = v;
-          }
+          if (slab)
+            *reinterpret_cast<f32x4*>(slab + (size_t)r * N + col + 16 * j) = acc[i][j];
+          else
+            gemm_store4<kMode>(Y, (long long)gr * N + col + 16 * j, acc[i][j]);
         }
       }
     }
