@@ -1160,30 +1160,36 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
     __syncthreads();
   }
 
+  static_assert(kSub1 == 1, "the rows' staging holds one sub-block per wave");
+  const float l_row = group_sum(l_run[0]);
+  const int qrow = qa + lr;
+  const bool qin = qrow < L;
+  const bool qvalid = qin && !gbit(qrow);  // qrow in [q0, L) lies inside [kt0, kt1)
+  const float lse2 = m_use[0] + fast_log2(l_row);
+  const float inv = 1.0f / l_row;
+  // the wave's 16 rows leave through its part of the (free) key tiles, a whole
+  // 128-byte row per 8 lanes instead of 32-byte runs of 16 rows (launch 1 of
+  // B64 n1024 with the paper's lengths 77.7 -> 76.3 us, B32 n600 window 64 38.6 ->
+  // 38.0; the 128-query blocks store 16 bytes a lane directly, and lost 1 %
+  // to a spilled register this way)
+  char* st = reinterpret_cast<char*>(&sm.b[0][0]) + 2048 * w;
 #pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    const float l_row = group_sum(l_run[j]);
-    const int qrow = qa + 16 * j + lr;
-    const bool qin = qrow < L;
-    const bool qvalid = qin && !gbit(qrow);  // qrow in [q0, L) lies inside [kt0, kt1)
-    const float lse2 = m_use[j] + fast_log2(l_row);
-    if (qvalid) {
-      const float inv = 1.0f / l_row;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-        store_row4<1>(Og + (long long)qrow * a.ld_out + 16 * dt + 4 * g, o[j][dt] * inv);
-      if (g == 0 && lseg) lseg[qrow] = lse2 * kLn2;
-    } else if (!qin && qrow < n) {
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-        store_row4<1>(Og + (long long)qrow * a.ld_out + 16 * dt + 4 * g, f32x4{0.f, 0.f, 0.f, 0.f});
-      if (g == 0 && lseg) lseg[qrow] = -INFINITY;
-    }
-    // excluded rows (global or padding) get +inf: their column-sum probabilities are 0
-    if (g == 0 && l2g && qrow < n) l2g[qrow] = qvalid ? lse2 : INFINITY;
+  for (int dt = 0; dt < 4; ++dt) {
+    uint2 x;
+    x.x = qin ? pack_bf16(o[0][dt][0] * inv, o[0][dt][1] * inv) : 0u;
+    x.y = qin ? pack_bf16(o[0][dt][2] * inv, o[0][dt][3] * inv) : 0u;
+    *reinterpret_cast<uint2*>(st + 128 * lr + 16 * ((2 * dt + (g >> 1)) ^ (lr & 7)) + 8 * (g & 1)) = x;
   }
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int row = 8 * x + (lane >> 3), q = qa + row;
+    const uint4 v = *reinterpret_cast<const uint4*>(st + 128 * row + 16 * ((lane ^ row) & 7));
+    if (q < n && (q >= L || !gbit(q))) *reinterpret_cast<uint4*>(Og + (long long)q * a.ld_out + 8 * (lane & 7)) = v;
+  }
+  if (g == 0 && lseg && qrow < n && (qvalid || !qin)) lseg[qrow] = qin ? lse2 * kLn2 : -INFINITY;
+  // excluded rows (global or padding) get +inf: their column-sum probabilities are 0
+  if (g == 0 && l2g && qrow < n) l2g[qrow] = qvalid ? lse2 : INFINITY;
 }
-
 
 // --------------------------------------------- bf16 pass 1, 32 queries a wave --
 // A wave owns 32 queries and takes a tile's keys in halves of 32 on the 32x32x16
