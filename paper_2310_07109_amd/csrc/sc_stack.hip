@@ -407,9 +407,9 @@ SC_DEV void gemm_tile(const __bf16* __restrict__ X, const __bf16* __restrict__ W
 // At most 168 VGPRs: three waves per SIMD, which the three workgroups per
 // CU that the stage buffers allow need.
 template <int kMode>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gemm_v3(const __bf16* __restrict__ X, const __bf16* __restrict__ W,
-                                                 void* __restrict__ Y, int B, int n, int K, int N,
-                                                 const int* __restrict__ len, const int* __restrict__ xidx, float* __restrict__ part) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gemm_v3(
+    const __bf16* __restrict__ X, const __bf16* __restrict__ W, void* __restrict__ Y, int B, int n, int K, int N,
+    const int* __restrict__ len, const int* __restrict__ xidx, float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) char stage[kStageBytes];
   __shared__ int grow[256], xrow[256];
   int* pre = reinterpret_cast<int*>(stage);  // until the first stage lands
@@ -674,9 +674,8 @@ __global__ __launch_bounds__(512) void k_gemm_v4(const __bf16* __restrict__ X, c
                                                  void* __restrict__ Y, int B, int n, int K, int N,
                                                  const int* __restrict__ len, const int* __restrict__ xidx,
                                                  float* __restrict__ part) {
-  extern __shared__ __attribute__((aligned(1024))) char sm4[];  // stages, two row tables, prefix table
-  int* rows = reinterpret_cast<int*>(sm4 + kStage4);
-  int* pre = rows + 1024;
+  __shared__ __attribute__((aligned(1024))) char sm4[kStage4];
+  __shared__ int rows[1024], pre[kMaxB4 + 1];  // two pairs of row tables; prefix table
   pack_prefix(pre, len, B, n);
   __syncthreads();
   const int R = __builtin_amdgcn_readfirstlane(pre[B]);
@@ -822,12 +821,7 @@ static bool gemm_v4_ok(int B, int n, int K, int N) {
 template <int kMode>
 static hipError_t launch_v4(const __bf16* x, const __bf16* w, void* y, int B, int n, int K, int N, const int* len,
                             const int* xidx, float* part, hipStream_t s) {
-  constexpr int kLds = kStage4 + 4096 + 4 * (kMaxB4 + 4);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_v4<kMode>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-  if (attr != hipSuccess) return attr;
-  const int lds = kStage4 + 4096 + 4 * (B + 4);
-  hipLaunchKernelGGL(k_gemm_v4<kMode>, dim3(kWgs4), dim3(512), lds, s, x, w, y, B, n, K, N, len, xidx, part);
+  hipLaunchKernelGGL(k_gemm_v4<kMode>, dim3(kWgs4), dim3(512), 0, s, x, w, y, B, n, K, N, len, xidx, part);
   return hipGetLastError();
 }
 
@@ -874,7 +868,8 @@ hipError_t launch_residual_layernorm(const void* x_res, const float* t, void* y,
   // table: 7.5 -> 6.3 us in the stack's late layers)
   const long long blocks = std::min<long long>((rows + 3) / 4, 1024);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), sizeof(int) * (B + 1), s,
-                     static_cast<const __bf16*>(x_res), t, static_cast<__bf16*>(y), B, n, D, eps, len, xidx, part, K, gemm_v4_ok(B, n, K, D) ? 1 : 0);
+                     static_cast<const __bf16*>(x_res), t, static_cast<__bf16*>(y), B, n, D, eps, len, xidx, part, K,
+                     gemm_v4_ok(B, n, K, D) ? 1 : 0);
   return hipGetLastError();
 }
 
