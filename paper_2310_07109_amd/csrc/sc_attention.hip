@@ -1370,16 +1370,30 @@ SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
       lds_dma16(g, (unsigned)min(k0 + R0 + 8, kt1 - 1) * ldb + u, l1);
     }
   };
-  // the rows of 64 listed positions (unused entries, -1, load row 0)
-  auto load_list = [&](const T* g, __bf16* tile, unsigned u, const int* pos) {
-    const unsigned l0 = lds_addr(tile + 16 * w * 64), l1 = l0 + 1024u;
-    lds_dma16(g, (unsigned)max(pos[R0], 0) * ldb + u, l0);
-    lds_dma16(g, (unsigned)max(pos[R0 + 8], 0) * ldb + u, l1);
+  // The rows of 64 listed positions.  An unused entry (-1) takes the block's
+  // first key as its K row (its logit is replaced by -inf) and zeros as its V
+  // row, which P V multiplies by 0: a row of the sequence there would hand an
+  // infinity or NaN in it to every query of the block.
+  auto load_list = [&](const int* pos, int lbuf) {
+    const int ln = opaque_lane();
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int p = pos[16 * w + 8 * x + (ln >> 3)];
+      const unsigned row = (unsigned)(p < 0 ? kt0 : p) * ldb;
+      __bf16 *kd = sm.b[lbuf] + (16 * w + 8 * x) * 64, *vd = sm.c[lbuf] + (16 * w + 8 * x) * 64;
+      lds_dma16(Kg, row + 16u * ((ln & 7) ^ (ln >> 3)), lds_addr(kd));
+      if (p >= 0)
+        lds_dma16(Vg, row + 16u * ((ln & 7) ^ v_swz(ln >> 3)), lds_addr(vd));
+      else
+        zero16(vd + 8 * ln);
+    }
   };
-  // slots of chunk c, one per lane (-1: unused)
+  // slots of chunk c, one per lane (-1: unused, or causal and after the block,
+  // where no query attends it)
+  const int pend = causal ? min(L, q0 + kBQ3) : L;
   auto slot_pos = [&](int c) {
     const int p = kBK * c + lane < G ? gpb[kBK * c + lane] : -1;
-    return p < L ? max(p, -1) : -1;
+    return p < pend ? max(p, -1) : -1;
   };
   // slots whose key lies outside the band of some query of the block
   auto outside = [&](int p) {
@@ -1455,8 +1469,7 @@ SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
       load_rows(Kg, sm.b[(t + 1) & 1], uk, kt0 + (t + 1) * kBK);
       load_rows(Vg, sm.c[(t + 1) & 1], uv, kt0 + (t + 1) * kBK);
     } else if (t + 1 < ns) {
-      load_list(Kg, sm.b[(t + 1) & 1], uk, sm.pos[0]);
-      load_list(Vg, sm.c[(t + 1) & 1], uv, sm.pos[0]);
+      load_list(sm.pos[0], (t + 1) & 1);
     }
     if (t >= ia && t < ib) {
       tile3(qf, kb, vb, koff, voff, a.c2, m_use, l_run, o);
@@ -1490,8 +1503,7 @@ SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
     if (need == 0ull) continue;
     if (w == 0) sm.pos[1][lane] = p;
     __syncthreads();
-    load_list(Kg, sm.b[0], uk, sm.pos[1]);
-    load_list(Vg, sm.c[0], uv, sm.pos[1]);
+    load_list(sm.pos[1], 0);
     wait_dma();
     __syncthreads();
     global_tile(kbuf, vbuf, sm.pos[1], need);

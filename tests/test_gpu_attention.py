@@ -444,3 +444,38 @@ def test_wide_query_blocks(n, lens, window, G, causal):
     check_out(out.float().cpu().numpy(), ro, "bf16", bf16_step=True)
     check_lse(lse.cpu().numpy(), rl, vl)
     check_scores(scores.cpu().numpy(), rs, vl)
+
+
+@pytest.mark.parametrize("n,window,gpos,causal,t", [
+    (4096, 64, [1000, 2000, 3000], 0, 0),             # unused slots beside used ones; the first token holds the infinity
+    (4096, 64, [10, 4000], 1, 4000),                  # causal: a global key after almost every query
+    (4224, 34, list(range(5, 4000, 57)), 0, 0),       # 71 slots: a second tile of which one half has unused slots
+    (4224, 34, list(range(5, 4200, 57)), 1, 3995),    # causal, 74 slots, a global key among them
+    (2048, 64, [1000, 2000], 0, 0),                   # 64-query blocks
+    (2048, 64, [10, 2000], 1, 2000),
+])
+def test_nonfinite_value_stays_near(n, window, gpos, causal, t):
+    """An infinity in one token's value row reaches the queries that attend the token, and beyond them at most those
+    whose block of queries reads the row as a neighbour (128 queries); every other row (but the global ones, which
+    read all keys) keeps its bits.  A masked pair's probability is 0, but 0 times infinity is NaN, so the rows that a
+    block loads in the place of unused global slots count too."""
+    cfg = si.AttnConfig("nonfinite", 43, 1, n, 2, 64, "bf16", window, (n, n), len(gpos), "random", input_scale=1.0)
+    inp = si.make_attention_inputs(cfg)
+    inp["global_pos"] = np.array([gpos], dtype=np.int32)
+    d = make_desc(inp)
+    d.causal = causal
+    q, k, v = (to_dev_storage(inp[x], "bf16") for x in ("q", "k", "v"))
+    ref = sc.sc_window_attention(d, q, k, v)[0].float().cpu().numpy()
+    assert np.isfinite(ref).all()
+    v[0, t] = float("inf")
+    out = sc.sc_window_attention(d, q, k, v)[0].float().cpu().numpy()
+    rows, r = np.arange(n), window // 2
+    is_glob = np.isin(rows, gpos)
+    sees = (np.abs(rows - t) <= r) | is_glob[t]
+    if causal:
+        sees &= rows >= t
+    may = sees | (np.abs(rows - t) <= r + 127) | is_glob
+    assert not np.isfinite(out[0, sees]).any(), "a query that attends the token has a finite output"
+    far = ~may
+    assert far.sum() > n // 2 or causal
+    assert np.array_equal(out[0, far], ref[0, far]), f"{(out[0, far] != ref[0, far]).any(axis=(1, 2)).sum()} rows changed"
