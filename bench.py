@@ -46,7 +46,7 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 KERNEL_SOURCES = ("paper_2310_07109_amd/csrc/sc_attention.hip", "paper_2310_07109_amd/csrc/sc_device.h",
                   "paper_2310_07109_amd/csrc/sc_internal.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "window_attention_seq4096_traffic.json")
-DOMINANT = "k_attn_fwd<1, 128, false>"
+DOMINANT = "k_attn_fwd<1, true, false>"
 
 
 # name -> (input config, workload description)

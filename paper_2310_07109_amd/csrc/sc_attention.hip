@@ -10,7 +10,7 @@
 //   R3  neither global, |i-j| <= r -> window kernel, band tiles
 //
 // Window kernel, one workgroup (4 waves) per (sequence, head, 64 queries; bf16
-// sequences padded to kWideMinN tokens or more: 128 queries, 32 per wave, on
+// sequences of more than kNarrowMaxLen tokens: 128 queries, 32 per wave, on
 // 32x32x16 products, see window_fwd_v3):
 //   pass 1  each wave owns 16 queries; K/V tiles of 64 keys are staged in LDS
 //           (double-buffered, the next tile's loads in flight during the
@@ -420,6 +420,27 @@ struct WinLoader {
   }
 };
 
+// Padding rows q0 .. q0 + kRows - 1 of a (sequence, head): zero output rows
+// (unless the caller never reads them), LSE -inf, and log2-LSE +inf, which
+// leaves them out of the column sums.
+template <int DT, int kRows>
+SC_DEV void pad_rows(const AttnArgs& a, int bh, int q0) {
+  using T = typename Tr<DT>::T;
+  constexpr int kEpc = 16 / sizeof(T), kCpr = kHeadDim / kEpc;
+  const int n = a.n, tid = threadIdx.x;
+  T* Og = static_cast<T*>(a.out) + (bh / a.H) * a.bs_out + (bh % a.H) * kHeadDim;
+  if (!a.skip_pad_out)
+    for (int c = tid; c < kRows * kCpr; c += kThreads) {
+      const int q = q0 + c / kCpr;
+      if (q < n) zero16(Og + (long long)q * a.ld_out + (c % kCpr) * kEpc);
+    }
+  for (int i = tid; i < kRows; i += kThreads)
+    if (q0 + i < n) {
+      if (a.lse) a.lse[(long long)bh * n + q0 + i] = -INFINITY;
+      if (a.win_lse2) a.win_lse2[(long long)bh * n + q0 + i] = INFINITY;
+    }
+}
+
 // Pass 1: O, LSE (and the log2 LSE used by the column sums) for the
 // non-global queries of the block; zero rows for padding queries.
 template <int DT>
@@ -438,18 +459,8 @@ SC_DEV void window_fwd_block(const AttnArgs& a, int bh, int qb, Smem<DT>& sm, ui
   float* lseg = a.lse ? a.lse + (long long)wb.bh * n : nullptr;
   float* l2g = a.win_lse2 ? a.win_lse2 + (long long)wb.bh * n : nullptr;
 
-  if (q0 >= L) {  // padding block: zero output rows (unless the caller never reads them)
-    constexpr int kEpc = 16 / sizeof(T), kCpr = kHeadDim / kEpc;
-    if (!a.skip_pad_out)
-      for (int c = tid; c < kBQ * kCpr; c += kThreads) {
-        const int q = q0 + c / kCpr;
-        if (q < n) zero16(Og + (long long)q * a.ld_out + (c % kCpr) * kEpc);
-      }
-    for (int i = tid; i < kBQ; i += kThreads)
-      if (q0 + i < n) {
-        if (lseg) lseg[q0 + i] = -INFINITY;
-        if (l2g) l2g[q0 + i] = INFINITY;
-      }
+  if (q0 >= L) {
+    pad_rows<DT, kBQ>(a, bh, q0);
     return;
   }
   uint32_t* sBits = sDyn;
@@ -932,17 +943,8 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
   float* lseg = a.lse ? a.lse + (long long)wb.bh * n : nullptr;
   float* l2g = a.win_lse2 ? a.win_lse2 + (long long)wb.bh * n : nullptr;
 
-  if (q0 >= L) {  // padding block: zero output rows (unless the caller never reads them)
-    if (!a.skip_pad_out)
-      for (int c = tid; c < kBQ2 * 8; c += kThreads) {
-        const int q = q0 + (c >> 3);
-        if (q < n) zero16(Og + (long long)q * a.ld_out + 8 * (c & 7));
-      }
-    for (int i = tid; i < kBQ2; i += kThreads)
-      if (q0 + i < n) {
-        if (lseg) lseg[q0 + i] = -INFINITY;
-        if (l2g) l2g[q0 + i] = INFINITY;
-      }
+  if (q0 >= L) {
+    pad_rows<1, kBQ2>(a, bh, q0);
     return;
   }
   uint32_t* sBits = sDyn;
@@ -1320,7 +1322,7 @@ SC_DEV void tile3_masked(const bf16x8 (&qf)[4], const char* kb, const char* vb, 
 // slots to a tile, each masked to the queries whose band does not hold it.
 SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
   using T = __bf16;
-  const int h = bh % a.H, b = bh / a.H;
+  const int b = __builtin_amdgcn_readfirstlane(bh / a.H), h = bh - b * a.H;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), gg = lane >> 5,
             lq = lane & 31;
   const int n = a.n, r = a.r, q0 = qb * kBQ3;
@@ -1329,17 +1331,8 @@ SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
   float* lseg = a.lse ? a.lse + (long long)bh * n : nullptr;
   float* l2g = a.win_lse2 ? a.win_lse2 + (long long)bh * n : nullptr;
 
-  if (q0 >= L) {  // padding block: zero output rows (unless the caller never reads them)
-    if (!a.skip_pad_out)
-      for (int c = tid; c < kBQ3 * 8; c += kThreads) {
-        const int q = q0 + (c >> 3);
-        if (q < n) zero16(Og + (long long)q * a.ld_out + 8 * (c & 7));
-      }
-    for (int i = tid; i < kBQ3; i += kThreads)
-      if (q0 + i < n) {
-        if (lseg) lseg[q0 + i] = -INFINITY;
-        if (l2g) l2g[q0 + i] = INFINITY;
-      }
+  if (q0 >= L) {
+    pad_rows<1, kBQ3>(a, bh, q0);
     return;
   }
   // reach of the band after the query: r, or 0 in the causal variant (where a
@@ -1385,7 +1378,7 @@ SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
       if (p >= 0)
         lds_dma16(Vg, row + 16u * ((ln & 7) ^ v_swz(ln >> 3)), lds_addr(vd));
       else
-        zero16(vd + 8 * ln);
+        *reinterpret_cast<uint4*>(vd + 8 * ln) = opaque_zero();
     }
   };
   // slots of chunk c, one per lane (-1: unused, or causal and after the block,
@@ -1540,29 +1533,38 @@ SC_DEV void window_fwd_v3(const AttnArgs& a, int bh, int qb, Smem<1>& sm) {
   if (gg == 0 && l2g && qrow < n) l2g[qrow] = qvalid ? lse2 : INFINITY;
 }
 
-// Work of launch 1 per (sequence, head) pair and key span: kSpanQB window
-// blocks, then the span's global-row blocks (one per 32-slot group).
 static_assert(kBQ == kBQ2 && kGlobalKeySpan % kBQ == 0 && kGlobalKeySpan % kBQ3 == 0,
               "window blocks tile the key span");
-struct FwdSpan {
-  int per;  // blocks per span
-};
 
-template <int BQ>
-__host__ __device__ inline FwdSpan fwd_span(const AttnArgs& a) {
-  return {kGlobalKeySpan / BQ + (a.n_gr > 0 ? a.ngc : 0)};
+// bf16 sequences of more than this many tokens run 128-query window blocks,
+// shorter ones 64-query blocks.  The two round differently (key tiles and
+// running maxima in another order), so the rule looks at the sequence's own
+// length: its result depends neither on the batch nor on the padded length it
+// comes in.  A 128-query block issues a third fewer VALU instructions per pair
+// (21.6M against 32.4M per launch at B8 n4096), which counts where a launch
+// has several rounds of blocks; a lone sequence makes one round, and its
+// 64-query blocks finish sooner.  Launch 1 between events, us, every sequence
+// on 64- and on 128-query blocks, H12, window 512 (window 128 with 32 slots):
+//   sequences of  1024               2049               3072               3749
+//    1            14.9/19.3 (12.6/13.9)  17.4/22.4 (14.4/15.7)  20.4/23.6 (16.4/16.4)  21.6/23.9 (17.6/16.5)
+//    4            21.2/23.5 (17.6/16.3)  31.3/31.7 (25.1/23.3)  39.5/42.1 (31.1/29.1)  46.1/46.8 (36.0/32.4)
+//   16            45.8/46.3 (38.9/35.0)  82.2/80.2 (64.5/56.2)   121/114.6 (92.7/81.8) 151.5/140.3 (114/101.4)
+// and B8 n4096 with 32 slots 90.3/84.  From 2048 tokens on batches gain what a
+// lone sequence below 4096 loses.  Launches that may hold both kinds run 3
+// waves per SIMD (165 VGPRs), where the 64-query blocks alone run 4: a batch
+// just above the line whose sequences mostly lie below it pays for that (B16
+// n2560, lengths 1280 to 2560: 99.7 -> 114).  At 4 waves for both (128 VGPRs) that
+// batch took 105, but B2 n8192 80 instead of 72.5.
+constexpr int kNarrowMaxLen = 2048;
+
+// Window-block indices of a (sequence, head) pair in a launch whose sequences
+// may be of either kind: the 128-query blocks of n tokens, and at least the
+// 64-query blocks of kNarrowMaxLen.  nspan: key spans the indices are spread over.
+constexpr int kNarrowBlocks = kNarrowMaxLen / kBQ;
+inline int wide_blocks(int n, int nspan) {
+  return std::max((n + kBQ3 - 1) / kBQ3, nspan * ((kNarrowBlocks + nspan - 1) / nspan));
 }
 
-// Launch 1: the window pass-1 blocks and the global-row forward blocks (when
-// there are global tokens).  Span by span (a.span_major: sequences up to
-// kSpanOrderMaxN tokens, and the pruned layers of a stack): a (sequence,
-// head) pair's work of key span c (kGlobalKeySpan keys) is the window blocks
-// of its queries, then the global-row blocks of its keys, which the window
-// blocks just read (they are still in the XCD's L2); the pairs are dealt
-// round-robin to the XCDs, a pair's work on one XCD (xcd_span_map).
-// Otherwise (longer sequences) the window blocks come first, pair by pair
-// (xcd_pair_map), and the global-row blocks last, where they fill the window
-// blocks' uneven tail.
 // Zeroes 16-byte units [kFillUnits blk, kFillUnits (blk + 1)) of p.  As part of
 // launch 1 the clearing of the band layout, which is bound by memory, runs in
 // the gaps of the attention, which is bound by latency and VALU issue (a
@@ -1575,12 +1577,22 @@ SC_DEV void fill_block(uint4* p, long long units, int blk) {
     if (u0 + i < units) p[u0 + i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// BQ: queries per window block.  kFill: blocks from nfwd on zero a.fill.
-template <int DT, int BQ, bool kFill>
+// Launch 1: the window pass-1 blocks and the global-row forward blocks (when
+// there are global tokens).  Span by span (a.span_major: sequences up to
+// kSpanOrderMaxN tokens, and the pruned layers of a stack): a (sequence,
+// head) pair's work of key span c (kGlobalKeySpan keys) is the window blocks
+// of its queries, then the global-row blocks of its keys, which the window
+// blocks just read (they are still in the XCD's L2); the pairs are dealt
+// round-robin to the XCDs, a pair's work on one XCD (xcd_span_map).
+// Otherwise (longer sequences) the window blocks come first, pair by pair
+// (xcd_pair_map), and the global-row blocks last, where they fill the window
+// blocks' uneven tail.
+// kWide: sequences may have 128-query blocks; kFill: blocks from nfwd on zero
+// a.fill.
+template <int DT, bool kWide, bool kFill>
 __global__ __launch_bounds__(kThreads) SC_OCC(DT == 1 ? 3 : 2) void k_attn_fwd(AttnArgs a, int nfwd) {
   __shared__ Smem<DT> sm;
   extern __shared__ uint32_t sDyn[];
-  constexpr int kSpanQB = kGlobalKeySpan / BQ;
   int bh, qb, gr = -1;  // a window block, or (gr >= 0) a global-row block
   if constexpr (kFill)
     if ((int)blockIdx.x >= nfwd) {  // the blocks past the attention's
@@ -1589,22 +1601,32 @@ __global__ __launch_bounds__(kThreads) SC_OCC(DT == 1 ? 3 : 2) void k_attn_fwd(A
     }
   if (a.span_major) {
     int c, o;
-    xcd_span_map(blockIdx.x, a.nkc, fwd_span<BQ>(a).per, a.H * a.B, bh, c, o);
-    if (o >= kSpanQB) gr = (bh * a.ngc + (o - kSpanQB)) * a.nkc + c;
-    qb = c * kSpanQB + o;
+    xcd_span_map(blockIdx.x, a.nkc, a.nsb + (a.n_gr > 0 ? a.ngc : 0), a.H * a.B, bh, c, o);
+    if (o >= a.nsb) gr = (bh * a.ngc + (o - a.nsb)) * a.nkc + c;
+    qb = c * a.nsb + o;
   } else {
     const int nwin = a.nqb * a.H * a.B;
     if ((int)blockIdx.x >= nwin) gr = blockIdx.x - nwin;
     xcd_pair_map(blockIdx.x, a.nqb, a.H * a.B, bh, qb);
   }
+  bh = __builtin_amdgcn_readfirstlane(bh);
+  qb = __builtin_amdgcn_readfirstlane(qb);
+  gr = __builtin_amdgcn_readfirstlane(gr);
   if (gr >= 0) {
     gr_fwd_block<DT>(a, gr, sm);
     return;
   }
-  if (qb >= a.nqb) return;  // the last span's missing query blocks
-  if constexpr (DT == 1 && BQ == kBQ3)
-    window_fwd_v3(a, bh, qb, sm);
-  else if constexpr (DT == 1)
+  if constexpr (kWide) {
+    if (__builtin_amdgcn_readfirstlane(clampi(a.valid_len[bh / a.H], 0, a.n)) > a.narrow_max) {
+      if (kBQ3 * qb < a.n) window_fwd_v3(a, bh, qb, sm);
+      return;
+    }
+    // the pair's nqb indices as 64-query blocks: they reach past the sequence,
+    // and the rows beyond them, all padding, are dealt to them too
+    if (kBQ * (a.nqb + qb) < a.n) pad_rows<DT, kBQ>(a, bh, kBQ * (a.nqb + qb));
+  }
+  if (kBQ * qb >= a.n) return;  // the last span's missing query blocks
+  if constexpr (DT == 1)
     window_fwd_v2(a, bh, qb, sm, sDyn);
   else
     window_fwd_block<DT>(a, bh, qb, sm, sDyn);
@@ -2479,19 +2501,6 @@ int profile_read(double* fwd_ms, double* cols_ms, long long cap, long long* call
 // L2 in the pair order.
 constexpr int kSpanOrderMaxN = 4096;
 
-// bf16 window blocks of 128 queries for sequences padded to this length or
-// more.  A 128-query block issues a third fewer VALU instructions per pair
-// (21.6M against 32.4M per launch at B8 n4096), which counts where a launch
-// has several rounds of blocks; in a launch of one round the 64-query blocks
-// finish sooner.  The rule looks at n alone, so that a sequence's result does
-// not depend on the batch it comes in.  Launch 1 between events, us, 64 and
-// 128 queries (H12): B8 n4096 window 512 with 32 slots 92.5 and 83.6, causal
-// 74.2 and 65.6, B2 H16 n8192 window 1024 with 64 slots 118.7 and 110.3, B1
-// n4096 24.4 and 24.4; but B1 n2048 17.9 and 19.8, B1 n1024 window 256 12.5
-// and 15.4 (B64 n1024 80.7 and 75.2), and the layer step of B1 n3749 causal
-// window 842 51.4 and 52.7.
-constexpr int kWideMinN = 4096;
-
 template <int DT>
 static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   AttnArgs a = a0;
@@ -2504,11 +2513,21 @@ static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   a.n_gcol = (cols && glob) ? a.nqr * a.ngc * a.H * a.B : 0;
   const int nxc = glob ? (a.G + kBK - 1) / kBK : 0;
   const long long pairs = (long long)a.H * a.B;
-  const bool wide = DT == 1 && a.n >= kWideMinN;
-  if (wide) a.nqb = (a.n + kBQ3 - 1) / kBQ3;
-  const size_t dyn = wide ? 0 : sizeof(uint32_t) * ((size_t)a.rwp / 32 + 2 + nxc + 1);
+  const bool wide = DT == 1 && a.n > kNarrowMaxLen;
+  // window-block indices per span, and of a pair over all spans or queries
+  a.nsb = wide ? wide_blocks(kGlobalKeySpan * a.nkc, a.nkc) / a.nkc : kGlobalKeySpan / kBQ;
+  a.nqb = a.span_major ? a.nsb * a.nkc : wide ? wide_blocks(a.n, 1) : a.nqb;
+  // the 64-query blocks' tables: key range and slot chunks; with slots for more
+  // than 16 KB of them every sequence takes the 128-query blocks
+  if (wide) a.rwp = std::min(a.rwp, kNarrowMaxLen);
+  size_t dyn = sizeof(uint32_t) * ((size_t)a.rwp / 32 + 2 + nxc + 1);
+  a.narrow_max = kNarrowMaxLen;
+  if (wide && dyn > 16384) {
+    a.narrow_max = 0;
+    dyn = 0;
+  }
   // the spans' block counts (the host checks that they fit the grid limits)
-  const int fwd_per = wide ? fwd_span<kBQ3>(a).per : fwd_span<kBQ>(a).per;
+  const int fwd_per = a.nsb + (a.n_gr > 0 ? a.ngc : 0);
   const unsigned fwd_blocks = (unsigned)(a.span_major ? a.nkc * fwd_per * pairs : a.n_gr + a.nqb * pairs);
   long long fill_blocks = a.fill ? (a.fill_units + kFillUnits - 1) / kFillUnits : 0;
   if (fwd_blocks + fill_blocks >= (1LL << 31)) {  // past the grid limit: a launch of its own
@@ -2520,9 +2539,9 @@ static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   const unsigned col_blocks = (unsigned)(a.span_major ? a.nkc * col_per * pairs
                                                       : ((a.n_gr + 7) & ~7) + a.n_bcol + a.n_gcol);
   if (!a.no_profile) profile_mark(s, 0);
-  constexpr int kBQW = DT == 1 ? kBQ3 : kBQ;
-  auto* fwd = fill_blocks > 0 ? (wide ? k_attn_fwd<DT, kBQW, true> : k_attn_fwd<DT, kBQ, true>)
-                              : (wide ? k_attn_fwd<DT, kBQW, false> : k_attn_fwd<DT, kBQ, false>);
+  constexpr bool kW = DT == 1;
+  auto* fwd = fill_blocks > 0 ? (wide ? k_attn_fwd<DT, kW, true> : k_attn_fwd<DT, false, true>)
+                              : (wide ? k_attn_fwd<DT, kW, false> : k_attn_fwd<DT, false, false>);
   hipLaunchKernelGGL(fwd, dim3((unsigned)(fwd_blocks + fill_blocks)), dim3(kThreads), dyn, s, a, (int)fwd_blocks);
   if (!a.no_profile) profile_mark(s, 1);
   if (col_blocks > 0) {

@@ -129,6 +129,14 @@ SC_DEV int opaque_lane() {
   return lane;
 }
 
+// 16 zero bytes, made where they are stored (a plain constant is hoisted and
+// held, or spilled, in four registers).
+SC_DEV uint4 opaque_zero() {
+  unsigned z;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+  return make_uint4(z, z, z, z);
+}
+
 // One direct load: lane i's 16 bytes at base + voff land at LDS byte address
 // lds + 16 i (gfx950 global_load_lds_dwordx4, destination base in m0).  Inline
 // assembly on purpose: the compiler cannot tell these writes from later LDS

@@ -36,6 +36,8 @@ struct AttnArgs {
   float* part_extra;      // [B, H, nqr, G] global-key columns per 512-query range
   float* part_grow;       // [B, H, ngc, n] column sums over the global rows
   int nqb, rwp, ngc, nkc, Gp, nkb, nqr;
+  int nsb;                // window-block indices of a pair per key span (launch 1)
+  int narrow_max;         // bf16 sequences up to this length run 64-query window blocks
   int n_gr, n_bcol, n_gcol;  // block counts of the global-row, band-column and global-column parts
   // global-row split partials (workspace)
   float* gr_ml;           // [B, H, nkc, Gp, 2]

@@ -427,9 +427,10 @@ def test_dispatch_order_invariance(causal):
     (4096, (2999, 257, 96, 0), 33, 0, 1),
 ])
 def test_wide_query_blocks(n, lens, window, G, causal):
-    """The 128-query window blocks (sequences padded to 4096 tokens or more): lengths at their edges, band edges
-    inside and between the 32-key halves, global keys inside and outside the bands.  Logits of order one (inputs
-    N(0, 1)), so that a key too many or too few moves the LSE beyond its tolerance."""
+    """Launches of 128-query window blocks for the sequences of more than 2048 tokens and 64-query blocks for the
+    others, padded to 4096 tokens or more: lengths at the blocks' edges, band edges inside and between the 32-key
+    halves, global keys inside and outside the bands.  Logits of order one (inputs N(0, 1)), so that a key too many or
+    too few moves the LSE beyond its tolerance."""
     cfg = si.AttnConfig("wide", 31, 4, n, 2, 64, "bf16", window, (n, n), G, "random", input_scale=1.0)
     inp = si.make_attention_inputs(cfg)
     vl = np.array(lens, dtype=np.int32)
@@ -479,3 +480,75 @@ def test_nonfinite_value_stays_near(n, window, gpos, causal, t):
     far = ~may
     assert far.sum() > n // 2 or causal
     assert np.array_equal(out[0, far], ref[0, far]), f"{(out[0, far] != ref[0, far]).any(axis=(1, 2)).sum()} rows changed"
+
+
+# Lengths about the line (2048 tokens) between 64- and 128-query window blocks, and about the edges of the latter's
+# blocks and 32-key halves beyond it, in launches of every index layout: 7, 6, 5 and 4 window-block indices per span, and
+# pair order; rows past the 64-query blocks' indices are padding that those blocks clear.
+@pytest.mark.parametrize("n,lens,window,G,causal", [
+    (2048, (2048, 2047, 1, 0), 33, 3, 0),             # no long sequence: the launch without 128-query blocks
+    (2049, (2049, 2048, 1, 0), 33, 3, 0),             # one query in the last block
+    (2600, (2600, 2081, 2111, 130), 64, 70, 1),       # two 64-slot tiles
+    (3590, (3500, 2144, 2048, 2177), 16, 33, 0),      # window edges on halves; 33 slots: one in the second half
+    (3968, (3968, 2500, 600, 2305), 400, 5, 0),       # the last length with more indices than 128-query blocks
+    (3969, (3969, 2049, 2048, 63), 0, 130, 0),        # window 0; three 64-slot tiles
+    (4096, (2999, 2208, 2176, 2048), 5000, 64, 0),    # the window covers the sequences: no key outside a band
+    (4224, (2050, 4224, 2048, 1999), 33, 33, 0),      # pair order
+    (4224, (64, 2240, 0, 4200), 64, 70, 1),
+])
+def test_block_kinds_by_length(n, lens, window, G, causal):
+    """Sequences on both sides of the line between 64- and 128-query blocks in one launch, against the oracle; inputs
+    N(0, 1) as above.  Every row is written: the outputs are NaN beforehand, and padding rows come out exactly 0."""
+    cfg = si.AttnConfig("kinds", 37, 4, n, 2, 64, "bf16", window, (n, n), G, "random", input_scale=1.0)
+    inp = si.make_attention_inputs(cfg)
+    vl = np.array(lens, dtype=np.int32)
+    inp["valid_len"], inp["global_pos"] = vl, si.global_positions(37, vl, G, "random")
+    d = make_desc(inp)
+    d.causal = causal
+    q, k, v = (to_dev_storage(inp[x], "bf16") for x in ("q", "k", "v"))
+    lse = torch.full((4, 2, n), float("nan"), device="cuda")
+    out, lse, sp, _ = sc.sc_window_attention(d, q, k, v, out=torch.full_like(q, float("nan")), lse=lse)
+    scores = sc.sc_ltp_score(d, sp)
+    ro, rl, rs = oracle.sparse_attention(inp["q64"], inp["k64"], inp["v64"], vl, inp["global_pos"], window,
+                                         inp["alpha"], causal=bool(causal))
+    o = out.float().cpu().numpy()
+    for b, L in enumerate(lens):
+        assert np.all(o[b, L:] == 0.0), f"padding rows of sequence {b}"
+    check_out(o, ro, "bf16", bf16_step=True)
+    check_lse(lse.cpu().numpy(), rl, vl)
+    check_scores(scores.cpu().numpy(), rs, vl)
+
+
+@pytest.mark.parametrize("window,G,causal", [(512, 32, 0), (65, 3, 0), (300, 70, 1)])
+def test_result_independent_of_padding_and_batch(window, G, causal):
+    """A sequence's output, LSE and scores do not depend on the padded length nor on the sequences beside it: alone
+    without padding, in batches padded to 2520 .. 4224 tokens, and with the batch in reverse order, bit for bit."""
+    lens, H = (2500, 2049, 2048, 1000, 65), 2
+    cfg = si.AttnConfig("padding", 47, len(lens), 2500, H, 64, "bf16", window, (2500, 2500), G, "random", input_scale=1.0)
+    inp = si.make_attention_inputs(cfg)
+    vl = np.array(lens, np.int32)
+    gp = si.global_positions(47, vl, G, "random")
+    src = [to_dev_storage(inp[x], "bf16") for x in ("q", "k", "v")]
+
+    def run(seqs, n):
+        args = [torch.zeros((len(seqs), n, H, 64), dtype=torch.bfloat16, device="cuda") for _ in src]
+        for a, t in zip(args, src):
+            for i, b in enumerate(seqs):
+                a[i, :lens[b]] = t[b, :lens[b]]
+        d = sc.Desc(len(seqs), n, H, window, dev_i32(vl[list(seqs)]), dev_i32(gp[list(seqs)]), inp["alpha"],
+                    sc.SC_BF16, causal=causal)
+        out, lse, sp, _ = sc.sc_window_attention(d, *args)
+        scores = sc.sc_ltp_score(d, sp)
+        return {b: (out[i, :lens[b]].view(torch.int16), lse[i, :, :lens[b]], scores[i, :lens[b]])
+                for i, b in enumerate(seqs)}
+
+    alone = {b: run([b], max(lens[b], G))[b] for b in range(len(lens))}
+    for n in (2520, 3500, 4095, 4096, 4224):
+        for seqs in (list(range(len(lens))), list(reversed(range(len(lens))))):
+            got = run(seqs, n)
+            for b in seqs:
+                for what, x, y in zip(("output", "lse", "scores"), alone[b], got[b]):
+                    assert torch.equal(x, y), f"{what} of sequence {b} ({lens[b]} tokens) differs at n = {n}"
+    short = {b: run([b], 2048)[b] for b in (2, 3, 4)}
+    for b in short:
+        assert all(torch.equal(x, y) for x, y in zip(alone[b], short[b])), f"sequence {b} differs at n = 2048"
