@@ -495,6 +495,9 @@ def test_nonfinite_value_stays_near(n, window, gpos, causal, t):
     (4096, (2999, 2208, 2176, 2048), 5000, 64, 0),    # the window covers the sequences: no key outside a band
     (4224, (2050, 4224, 2048, 1999), 33, 33, 0),      # pair order
     (4224, (64, 2240, 0, 4200), 64, 70, 1),
+    (2600, (2600, 2300, 2049, 700), 64, 600, 0),      # slot tiles with all, some and none of their keys outside the bands
+    (2600, (2600, 2300, 2049, 700), 64, 600, 1),
+    (2112, (2112, 2050, 33, 0), 32, 2112, 0),         # all tokens global
 ])
 def test_block_kinds_by_length(n, lens, window, G, causal):
     """Sequences on both sides of the line between 64- and 128-query blocks in one launch, against the oracle; inputs
