@@ -2521,6 +2521,10 @@ int profile_read(double* fwd_ms, double* cols_ms, long long cap, long long* call
 // L2 in the pair order.
 constexpr int kSpanOrderMaxN = 4096;
 
+// Blocks a launch may have: a grid counts its threads in 32 bits, and a larger
+// one runs its remainder without an error.
+constexpr long long kMaxBlocks = ((1LL << 32) - 1) / kThreads;
+
 template <int DT>
 static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   AttnArgs a = a0;
@@ -2550,14 +2554,15 @@ static hipError_t launch_window_t(const AttnArgs& a0, hipStream_t s) {
   const int fwd_per = a.nsb + (a.n_gr > 0 ? a.ngc : 0);
   const unsigned fwd_blocks = (unsigned)(a.span_major ? a.nkc * fwd_per * pairs : a.n_gr + a.nqb * pairs);
   long long fill_blocks = a.fill ? (a.fill_units + kFillUnits - 1) / kFillUnits : 0;
-  if (fwd_blocks + fill_blocks >= (1LL << 31)) {  // past the grid limit: a launch of its own
+  const int col_per = a.bp_band ? col_span<DT, true>(a).per : col_span<DT, false>(a).per;
+  const unsigned col_blocks = (unsigned)(a.span_major ? a.nkc * col_per * pairs
+                                                      : ((a.n_gr + 7) & ~7) + a.n_bcol + a.n_gcol);
+  if (fwd_blocks > kMaxBlocks || col_blocks > kMaxBlocks) return hipErrorInvalidConfiguration;
+  if (fwd_blocks + fill_blocks > kMaxBlocks) {  // a launch of its own
     const hipError_t e = launch_fill_zero(a.fill, (size_t)a.fill_units * 16, s);
     if (e != hipSuccess) return e;
     fill_blocks = 0;
   }
-  const int col_per = a.bp_band ? col_span<DT, true>(a).per : col_span<DT, false>(a).per;
-  const unsigned col_blocks = (unsigned)(a.span_major ? a.nkc * col_per * pairs
-                                                      : ((a.n_gr + 7) & ~7) + a.n_bcol + a.n_gcol);
   if (!a.no_profile) profile_mark(s, 0);
   constexpr bool kW = DT == 1;
   auto* fwd = fill_blocks > 0 ? (wide ? k_attn_fwd<DT, kW, true> : k_attn_fwd<DT, false, true>)

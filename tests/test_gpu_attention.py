@@ -555,3 +555,17 @@ def test_result_independent_of_padding_and_batch(window, G, causal):
     short = {b: run([b], 2048)[b] for b in (2, 3, 4)}
     for b in short:
         assert all(torch.equal(x, y) for x, y in zip(alone[b], short[b])), f"sequence {b} differs at n = 2048"
+
+
+def test_band_clearing_beside_a_full_grid():
+    """One-token sequences so many that the attention's blocks alone fit a launch (2^24 - 1 blocks of 256 threads) and
+    those that clear the band layout beside them do not: O = V, P = 1, and every entry of the NaN-filled layout is
+    written."""
+    B = 2097148
+    q, v = (torch.randn((B, 1, 1, 64), device="cuda").to(torch.bfloat16) for _ in range(2))
+    d = sc.Desc(B, 1, 1, 0, torch.ones(B, dtype=torch.int32, device="cuda"), None, 0.125, sc.SC_BF16)
+    assert sc.sc_band_probs_size(d) == 4 * B
+    band = torch.full((B,), float("nan"), device="cuda")
+    out = sc.sc_window_attention(d, q, q, v, score_partials=False, band_probs=band)[0]
+    assert torch.equal(out, v)
+    assert float((band - 1).abs().max()) <= 1e-5
