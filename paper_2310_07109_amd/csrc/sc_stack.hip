@@ -466,12 +466,14 @@ constexpr int kWgs4 = 256;       // one workgroup per CU, each taking items in t
 // and 237 (larger tiles of this kernel, 256 x 128 and 256 x 256, did not beat
 // k_gemm_v3's three workgroups per CU: 572 against 620 at 24 576 rows).
 constexpr int kV4Rows = 4096;
-// Microseconds of a K stage per mode, and of an item beside its stages,
-// fitted to measured launches; the plan takes the cheapest mode and split by
-// rounds x (stages x stage + 2).  Splits (float32 outputs with slabs) as in
-// k_gemm_v3: S workgroups take K / S each, the LayerNorm adds the slabs, which
-// costs it about 0.1 us per 1024 rows of slab.
-SC_DEV float stage_us4(int m) { return m == 0 ? 0.33f : m == 1 ? 0.21f : 0.15f; }
+// Hundredths of a microsecond of a K stage per mode, and of an item beside its
+// stages, fitted to measured launches; the plan takes the cheapest mode and
+// split by rounds x (stages x stage + 200).  Splits (float32 outputs with slabs)
+// as in k_gemm_v3: S workgroups take K / S each, the LayerNorm adds the slabs,
+// which costs it about 0.1 us per 1024 rows of slab.  The product and the
+// LayerNorm price the plan each for itself, so it is priced in whole numbers:
+// two modes may cost the same, and both kernels have to settle it alike.
+SC_DEV int stage_cost4(int m) { return m == 0 ? 33 : m == 1 ? 21 : 15; }
 SC_DEV Plan4 gemm_plan4(int R, int N, int nk, bool split) {
   // lane 4 m + s prices mode m with S = 2^s; the cheapest wins (ties: the lower lane)
   const int lane = threadIdx.x & 63, m = (lane >> 2) & 3, S = 1 << (lane & 3);
@@ -481,10 +483,11 @@ SC_DEV Plan4 gemm_plan4(int R, int N, int nk, bool split) {
   ok = ok && (S == 1 || split);
   ok = ok && (S == 1 || (long long)T * bm * S <= kGemmSplitRows);
   const int rounds = (T * (N / bn) * S + kWgs4 - 1) / kWgs4;
-  float t = rounds * (per * stage_us4(m) + 2.0f) + (S > 1 ? 0.4f * S * T * bm / 4096.f : 0.f);
-  if (!ok) t = 1e30f;
+  // in eighths of a hundredth: 0.4 us per 4096 rows of slab are 5 per 64
+  int t = 8 * rounds * (per * stage_cost4(m) + 200) + (S > 1 ? 5 * S * (T * bm / 64) : 0);
+  if (!ok) t = 0x7fffffff;
   int best = lane & 15;
-  auto meet = [&](float to, int bo) {
+  auto meet = [&](int to, int bo) {
     const bool take = to < t || (to == t && bo < best);
     t = take ? to : t;
     best = take ? bo : best;

@@ -252,6 +252,8 @@ def test_split_reduction_full_layers():
     (12, 3072, (33, 31)),                # RoBERTa widths on one tile: the widest split
     (12, 3072, (700, 650, 640)),         # several items per workgroup
     (6, 768, (1024, 1023, 1000, 1025)),  # more than 4096 padded rows: the three-workgroup product
+    (4, 256, (800, 700)),                # one and two ranges of W2's reduction (and of Wo's) are priced alike
+    (2, 512, (800, 700)),                # two and four ranges of W2's
 ])
 def test_products_of_few_rows(H, F, lens):
     """One unpruned full layer at the edges of the small products' tiles, splits and row limit."""
