@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const __bf16* __restrict__ X,
       const int m = m0 + row;
       __bf16* d = sX + row * kGPitch + 8 * part;
       if (m < rows && k0 + 8 * part < K)
-        copy16(d, Xb + (long long)(xidx ? xidx[(long long)b * n + m] : m) * K + k0 + 8 * part);
+        copy16(d, Xb + (long long)(xidx ? clampi(xidx[(long long)b * n + m], 0, n - 1) : m) * K + k0 + 8 * part);
       else
         zero16(d);
     }

@@ -272,3 +272,20 @@ def test_products_of_few_rows(H, F, lens):
     yy = to_f64(y, vl)
     for b, L in enumerate(lens):
         check_out(yy[b, :L], ry[b, :L], "bf16", what=f"sequence {b}", bf16_step=True)
+
+
+@pytest.mark.parametrize("H,F", [(3, 0), (3, 256), (1, 0), (1, 192)])
+def test_pruned_layers_of_odd_width(H, F):
+    """Two pruned layers whose width (64 H) is no multiple of 128: the output projection takes the unpacked product,
+    which reads the kept rows through keep_idx (as the residual LayerNorm does, without slabs).  Ragged lengths, with
+    sequences of one token and none."""
+    lens = (190, 1, 0, 147)
+    cfg = si.StackConfig("odd", 53, len(lens), 190, H, 64, 2, 32, (190, 190), 1, 0.08, 0.0, ffn_dim=F,
+                         windows=(32, 64) if F else None)
+    inp = si.make_stack_inputs(cfg)
+    vl = np.array(lens, np.int32)
+    gp = si.global_positions(53, vl, 1, "first")
+    ffn = dict(w1_bits=inp["w1"], w2_bits=inp["w2"], windows=[32, 64]) if F else {}
+    _, left = layerwise(inp["x"], inp["wqkv"], inp["wo"], vl, gp, H, 32, cfg.alpha, [0.0055, 0.009],
+                        tag=f"odd width H{H} F{F}", **ffn)
+    assert 1 < left[0] < 190 and 1 < left[3] < 147, "the thresholds prune some tokens and keep some"
