@@ -569,3 +569,62 @@ def test_band_clearing_beside_a_full_grid():
     out = sc.sc_window_attention(d, q, q, v, score_partials=False, band_probs=band)[0]
     assert torch.equal(out, v)
     assert float((band - 1).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,n,window,G,offset", [
+    (1, 1, 101, 20, 2, 0),   # an odd number of entries: cleared in a launch of its own
+    (2, 2, 300, 33, 3, 1),   # a buffer that starts 4 bytes past a 16-byte boundary: likewise
+    (2, 2, 300, 33, 3, 4),   # 16 bytes past the allocation's start: cleared inside launch 1
+    (1, 1, 63, 4, 1, 3),     # fewer entries than one clearing block, odd start
+])
+def test_band_layout_is_cleared(dtype, B, H, n, window, G, offset):
+    """Every entry of the layout against float64 probabilities, in a NaN-filled buffer at each alignment: entries without
+    an allowed pair are exactly 0, and nothing outside the layout is written."""
+    lens = [n] if B == 1 else [n, n - 41]
+    inp = small_case("clear", dtype, B, n, H, window, G, (n, n), lens=lens)
+    d = make_desc(inp)
+    q, k, v = (to_dev_storage(inp[x], dtype) for x in ("q", "k", "v"))
+    size = sc.sc_band_probs_size(d) // 4
+    buf = torch.full((size + offset + 8,), float("nan"), device="cuda")
+    sc.sc_window_attention(d, q, k, v, band_probs=buf[offset:offset + size])
+    got = buf.cpu().numpy()
+    assert np.isnan(got[:offset]).all() and np.isnan(got[offset + size:]).all()
+    got = got[offset:offset + size]
+    r, bw = window // 2, 2 * (window // 2) + 1
+    want = np.zeros(size)
+    band = want[:B * H * n * bw].reshape(B, H, n, bw)
+    gcol = want[B * H * n * bw:B * H * n * (bw + G)].reshape(B, H, n, G)
+    grow = want[B * H * n * (bw + G):].reshape(B, H, G, n)
+    i, j = np.arange(n)[:, None], np.arange(n)[None, :]
+    for b, L in enumerate(lens):
+        gp = [int(p) for p in inp["global_pos"][b] if p >= 0]
+        glob = np.isin(np.arange(n), gp)
+        allowed = ((np.abs(i - j) <= r) | glob[:, None] | glob[None, :]) & (i < L) & (j < L)
+        for h in range(H):
+            s = np.where(allowed, inp["alpha"] * inp["q64"][b, :, h] @ inp["k64"][b, :, h].T, -np.inf)
+            with np.errstate(invalid="ignore"):
+                P = np.exp(s - s.max(axis=1, keepdims=True))
+                P = np.nan_to_num(P / P.sum(axis=1, keepdims=True))
+            plain = np.where(allowed & ~glob[:, None] & ~glob[None, :], P, 0.0)
+            for o in range(-r, r + 1):
+                rows = np.arange(max(0, -o), min(n, n - o))
+                band[b, h, rows, o + r] = plain[rows, rows + o]
+            for slot, p in enumerate(gp):
+                gcol[b, h, :, slot] = np.where(glob, 0.0, P[:, p])
+                grow[b, h, slot] = P[p]
+    assert np.all(got[want == 0.0] == 0.0)
+    np.testing.assert_allclose(got, want, rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_band_layout_pair_order(dtype):
+    """The band layout, cleared beside the attention, in the pair-by-pair dispatch of sequences above 4096 tokens."""
+    inp = small_case("pair band", dtype, 2, 4164, 1, 40, 5, (2000, 4164), lens=[4164, 2001])
+    ro, rl, rs = oracle.sparse_attention(inp["q64"], inp["k64"], inp["v64"], inp["valid_len"], inp["global_pos"], 40,
+                                         inp["alpha"])
+    g = run_attention(inp, band=True)
+    check_out(g["out"], ro, dtype)
+    check_lse(g["lse"], rl, inp["valid_len"])
+    check_scores(g["scores"], rs, inp["valid_len"])
+    check_scores(g["band_scores"], rs, inp["valid_len"])
