@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 }
 
 // ---------------------------------------------------------------------------
-// k_gemm_v4: the packed product for calls of at most kV4Rows rows.  Few rows
+// k_gemm_v4: the packed product for calls of few rows (kV4Rows, kV4Tiles).  Few rows
 // make few tiles, and a tile's time is then the round trips of its loads, a
 // microsecond or more each (the weights come from beyond the L2): k_gemm_v3
 // keeps 36 KB of stages in flight per workgroup.  Here one workgroup of 512
@@ -460,12 +460,22 @@ constexpr int kGK4 = 64;
 constexpr int kStage4 = 147456;  // stage buffers: 4 x 32 KB, 6 x 24 KB or 9 x 16 KB
 constexpr int kMaxB4 = 2048;     // sequences whose prefix table fits beside them
 constexpr int kWgs4 = 256;       // one workgroup per CU, each taking items in turn
-// Rows (B n) up to which k_gemm_v4 takes the product.  A 12-layer encoder's layer
-// with every row kept, D 768, FFN 3072, us with k_gemm_v3 and v4: 512 rows
-// 90.7 and 82.7, 1024 107 and 93, 2048 131 and 121, 4096 166 and 162; 6144 218
-// and 237 (larger tiles of this kernel, 256 x 128 and 256 x 256, did not beat
-// k_gemm_v3's three workgroups per CU: 572 against 620 at 24 576 rows).
-constexpr int kV4Rows = 4096;
+// Padded rows (B n), and 128 x 128 tiles of them, up to which k_gemm_v4 takes the
+// product: at most two rounds of its workgroups.  us with k_gemm_v3 and v4,
+// weights of 8 layers in turn, every row kept, tiles in brackets: QKV at D 768
+// 1536 rows (216) 17.3 and 14.0, 2048 (288) 18.5 and 23.2, 4096 (576) 26.2 and 32.8;
+// W1 there 1024 rows (192) 18.8 and 15.0, 2048 (384) 22.6 and 24.4, 4096 (768) 31.9
+// and 37.1; Wo with its LayerNorm 4096 rows (192) 27.3 and 23.5, W2 42.4 and 39.0.
+// Between one and two rounds v4 loses with every row kept and gains once a
+// layer has pruned (the rows left are known on the device only): 12 layers of
+// B1 n2048 D 1024 FFN 4096 with pruning, us with v3, v4 up to 256, 512 and any
+// number of tiles: 1548, 1420, 1369, 1368; 4 unpruned layers of B4 n1024 there
+// 772, -, 779, 838.  Larger tiles of this kernel (256 x 128, 256 x 256) did not beat
+// k_gemm_v3's three workgroups per CU at 24 576 rows (620 against 572 per layer).
+// A workgroup takes its CU's whole LDS, but several calls at once still gain:
+// the 12-layer encoder of B1 n512 on 1, 2 and 4 streams 1106, 609 and 367 us per
+// call with k_gemm_v3, 864, 504 and 340 with this kernel.
+constexpr int kV4Rows = 4096, kV4Tiles = 2 * kWgs4;
 // Hundredths of a microsecond of a K stage per mode, and of an item beside its
 // stages, fitted to measured launches; the plan takes the cheapest mode and
 // split by rounds x (stages x stage + 200).  Splits (float32 outputs with slabs)
@@ -818,7 +828,8 @@ bool gemm_v3_ok(int B, int n, int K, int N) {
 // Shapes of k_gemm_v4: as k_gemm_v3 with K whole stages of 64 (two at least),
 // few rows, and a batch whose prefix table fits beside the stage buffers.
 static bool gemm_v4_ok(int B, int n, int K, int N) {
-  return gemm_v3_ok(B, n, K, N) && K % kGK4 == 0 && K >= 2 * kGK4 && B <= kMaxB4 && (long long)B * n <= kV4Rows;
+  return gemm_v3_ok(B, n, K, N) && K % kGK4 == 0 && K >= 2 * kGK4 && B <= kMaxB4 && (long long)B * n <= kV4Rows &&
+         ((long long)B * n + 127) / 128 * (N / kBN) <= kV4Tiles;
 }
 
 template <int kMode>

@@ -254,6 +254,7 @@ def test_split_reduction_full_layers():
     (6, 768, (1024, 1023, 1000, 1025)),  # more than 4096 padded rows: the three-workgroup product
     (4, 256, (800, 700)),                # one and two ranges of W2's reduction (and of Wo's) are priced alike
     (2, 512, (800, 700)),                # two and four ranges of W2's
+    (6, 2304, (1000, 990, 980, 970)),    # W1 has too many tiles for the few-row product, the others not
 ])
 def test_products_of_few_rows(H, F, lens):
     """One unpruned full layer at the edges of the small products' tiles, splits and row limit."""
