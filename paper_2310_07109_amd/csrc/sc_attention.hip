@@ -754,116 +754,90 @@ SC_DEV void gr_fwd_block(const AttnArgs& a, int lin, Smem<DT>& sm) {
 
 
 // ----------------------------------------------------------- bf16 pass 1 --
-// A wave owns kSub1 16-query sub-blocks that share every K fragment and every
-// V read.  K/V tiles reach LDS
+// 64-query blocks: a wave owns 16 queries.  K/V tiles reach LDS
 // through the direct global->LDS loads of gfx950, without staging registers:
 // lane i of a wave load fills the 16 bytes at base + 16 i, so the swizzled
 // layout is produced by choosing which 16-byte unit of its row lane i fetches.
-// 16-query sub-blocks per wave.  Two share every K fragment and V read
-// (two MFMAs per LDS read) but need 168 VGPRs (3 waves per SIMD); one needs
-// 118 (4 waves per SIMD), which measured 3-5 % faster.
-constexpr int kSub1 = 1;
-constexpr int kBQ2 = 64 * kSub1;  // queries per block
+// (Two 16-query sub-blocks per wave, which share every K fragment and V read,
+// need 168 VGPRs, 3 waves per SIMD; one needs 118, 4 waves per SIMD, which
+// measured 3-5 % faster.  32 queries on 32x32x16 products: see window_fwd_v3.)
+constexpr int kBQ2 = 64;  // queries per block
 
-// One 64-key tile for the query sub-blocks of a wave.  Bit st of `live`
-// (wave-uniform) says whether 16-key sub-tile st can hold an allowed pair; in
-// masked tiles ok(j, st, i) decides the pair (sub-block j's query, key
-// 16 st + 4g + i).  Disallowed logits become -inf, which exp2 maps to 0
-// (c2 > 0 is guaranteed by the host).
-// S^T = K Q^T of one 64-key tile for both sub-blocks; dead sub-tiles give 0.
+// S^T = K Q^T of one 64-key tile; dead sub-tiles (see softmax_tile2) give 0.
 // kNst: the tile's first kNst 16-key sub-tiles are computed (4: the whole
 // tile; 2: keys 0..31, for gathered global keys that fill half a tile).
 template <bool kMasked, int kNst = 4>
-SC_DEV void qk_tile2(const bf16x8 (&qf)[kSub1][2], const __bf16* sK, int lr_in, int g_in, unsigned live,
-                     f32x4 (&s)[kSub1][4]) {
+SC_DEV void qk_tile2(const bf16x8 (&qf)[2], const __bf16* sK, int lr_in, int g_in, unsigned live, f32x4 (&s)[4]) {
   using TR = Tr<1>;
   auto is_live = [&](int st) { return !kMasked || ((live >> st) & 1u); };
   const int lr = lr_in, g = g_in;
 #pragma unroll
   for (int st = 0; st < kNst; ++st) {
-#pragma unroll
-    for (int j = 0; j < kSub1; ++j) s[j][st] = f32x4{0.f, 0.f, 0.f, 0.f};
+    s[st] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (is_live(st)) {
       bf16x8 kf[2];
       TR::load_frags(sK, 16 * st + lr, g, kf);
-#pragma unroll
-      for (int j = 0; j < kSub1; ++j) {
-        s[j][st] = TR::mma(kf[0], qf[j][0], s[j][st]);
-        s[j][st] = TR::mma(kf[1], qf[j][1], s[j][st]);
-      }
+      s[st] = TR::mma(kf[0], qf[0], s[st]);
+      s[st] = TR::mma(kf[1], qf[1], s[st]);
     }
   }
 }
 
-// Row maxima of a tile in log2 units (per sub-block).
-// Maxima of the lane's own logits of a tile (raw, unscaled), per sub-block.
+// Maximum of the lane's own logits of a tile (raw, unscaled).
 // (a tree of three-input maxima: 8 for 16 values, 4 for 8)
 template <int kNst = 4>
-SC_DEV void lane_max2(const f32x4 (&s)[kSub1][4], float (&lmax)[kSub1]) {
+SC_DEV void lane_max2(const f32x4 (&s)[4], float& lmax) {
   auto max3 = [](float a, float b, float c) { return vmax(vmax(a, b), c); };
+  float v[16];
 #pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    float v[16];
+  for (int st = 0; st < kNst; ++st)
 #pragma unroll
-    for (int st = 0; st < kNst; ++st)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[4 * st + i] = s[j][st][i];
-    if constexpr (kNst == 4) {
-      const float r0 = max3(v[0], v[1], v[2]), r1 = max3(v[3], v[4], v[5]), r2 = max3(v[6], v[7], v[8]);
-      const float r3 = max3(v[9], v[10], v[11]), r4 = max3(v[12], v[13], v[14]);
-      lmax[j] = vmax(max3(r0, r1, r2), max3(r3, r4, v[15]));
-    } else {
-      lmax[j] = max3(max3(v[0], v[1], v[2]), max3(v[3], v[4], v[5]), vmax(v[6], v[7]));
-    }
+    for (int i = 0; i < 4; ++i) v[4 * st + i] = s[st][i];
+  if constexpr (kNst == 4) {
+    const float r0 = max3(v[0], v[1], v[2]), r1 = max3(v[3], v[4], v[5]), r2 = max3(v[6], v[7], v[8]);
+    const float r3 = max3(v[9], v[10], v[11]), r4 = max3(v[12], v[13], v[14]);
+    lmax = vmax(max3(r0, r1, r2), max3(r3, r4, v[15]));
+  } else {
+    lmax = max3(max3(v[0], v[1], v[2]), max3(v[3], v[4], v[5]), vmax(v[6], v[7]));
   }
 }
 
-// Raises every running maximum below its tile maximum to it and rescales the
-// sums and accumulators (lanes that do not need it scale by 1).  lmax: the
-// lanes' own maxima; the tile maximum of a query is taken over its 4 lane
+// Raises a running maximum below its tile maximum to it and rescales the
+// sum and accumulators (lanes that do not need it scale by 1).  lmax: the
+// lane's own maximum; the tile maximum of a query is taken over its 4 lane
 // groups here.
-SC_DEV void raise2(const float (&lmax)[kSub1], float c2, float (&m_use)[kSub1], float (&l_run)[kSub1],
-                   f32x4 (&o)[kSub1][4]) {
-  float tmax[kSub1];
+SC_DEV void raise2(float lmax, float c2, float& m_use, float& l_run, f32x4 (&o)[4]) {
+  const float tmax = group_max(lmax) * c2;
+  const bool up = tmax > m_use;
+  const float f = up ? fast_exp2(m_use - tmax) : 1.0f;
+  m_use = up ? tmax : m_use;
+  l_run *= f;
 #pragma unroll
-  for (int j = 0; j < kSub1; ++j) tmax[j] = group_max(lmax[j]) * c2;
-#pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    const bool up = tmax[j] > m_use[j];
-    const float f = up ? fast_exp2(m_use[j] - tmax[j]) : 1.0f;
-    m_use[j] = up ? tmax[j] : m_use[j];
-    l_run[j] *= f;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) o[j][dt] *= f;
-  }
+  for (int dt = 0; dt < 4; ++dt) o[dt] *= f;
 }
 
 // P = exp2(S c2 - m) as bf16 MFMA operands, and each query's sum of the
 // lane's own P (float32, before rounding).
 template <int kNst = 4>
-SC_DEV void exp_tile2(const f32x4 (&s)[kSub1][4], float c2, const float (&m_use)[kSub1], bf16x8 (&pb)[kSub1][2],
-                      float (&part)[kSub1]) {
+SC_DEV void exp_tile2(const f32x4 (&s)[4], float c2, float m_use, bf16x8 (&pb)[2], float& part) {
+  float ps[4];
 #pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    float ps[4];
+  for (int st = 0; st < kNst; ++st) {
+    float p[4];
 #pragma unroll
-    for (int st = 0; st < kNst; ++st) {
-      float p[4];
+    for (int i = 0; i < 4; ++i) p[i] = fast_exp2(fmaf(s[st][i], c2, -m_use));
+    ps[st] = (p[0] + p[1]) + (p[2] + p[3]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) p[i] = fast_exp2(fmaf(s[j][st][i], c2, -m_use[j]));
-      ps[st] = (p[0] + p[1]) + (p[2] + p[3]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) pb[j][st >> 1][4 * (st & 1) + i] = (__bf16)p[i];
-    }
-    part[j] = kNst == 4 ? (ps[0] + ps[1]) + (ps[2] + ps[3]) : ps[0] + ps[1];
+    for (int i = 0; i < 4; ++i) pb[st >> 1][4 * (st & 1) + i] = (__bf16)p[i];
   }
+  part = kNst == 4 ? (ps[0] + ps[1]) + (ps[2] + ps[3]) : ps[0] + ps[1];
 }
 
 // O^T += V^T P^T for one tile: the V operand comes from transposed reads of
 // the row-major tile; lane (g, lr) supplies dims 16dt + 4(lr&3) .. +3 of rows
 // 32kc + 4g + lr/4 and 32kc + 16 + 4g + lr/4 (keys in MFMA order)
 template <bool kMasked, int kNst = 4>
-SC_DEV void pv_tile2(const bf16x8 (&pb)[kSub1][2], const __bf16* sV, f32x4 (&o)[kSub1][4], unsigned live) {
+SC_DEV void pv_tile2(const bf16x8 (&pb)[2], const __bf16* sV, f32x4 (&o)[4], unsigned live) {
   using TR = Tr<1>;
   auto is_live = [&](int st) { return !kMasked || ((live >> st) & 1u); };
   const int ln = threadIdx.x & 63, lr = ln & 15, g = ln >> 4;
@@ -876,15 +850,14 @@ SC_DEV void pv_tile2(const bf16x8 (&pb)[kSub1][2], const __bf16* sV, f32x4 (&o)[
       const i16x4 a0 = lds_read_tr16(sV + TR::off(vr, 2 * dt + b) + e);
       const i16x4 a1 = lds_read_tr16(sV + TR::off(vr + 16, 2 * dt + b) + e);
       const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-      for (int j = 0; j < kSub1; ++j) o[j][dt] = TR::mma(vf, pb[j][kc], o[j][dt]);
+      o[dt] = TR::mma(vf, pb[kc], o[dt]);
     }
   }
 }
 
-// One 64-key tile for the query sub-blocks of a wave.  Bit st of `live`
+// One 64-key tile for the wave's queries.  Bit st of `live`
 // (wave-uniform) says whether 16-key sub-tile st can hold an allowed pair; in
-// masked tiles ok(j, st, i) decides the pair (sub-block j's query, key
+// masked tiles ok(st, i) decides the pair (the lane's query, key
 // 16 st + 4g + i).  Disallowed logits become -inf, which exp2 maps to 0
 // (c2 > 0 is guaranteed by the host).  P is computed with the running max
 // first; a logit more than kTau above it makes the lane's sum of P exceed
@@ -892,34 +865,28 @@ SC_DEV void pv_tile2(const bf16x8 (&pb)[kSub1][2], const __bf16* sV, f32x4 (&o)[
 // the tile maxima taken, the running maxima raised to them and P recomputed.
 // So every P stays below 2^kTau, and the maxima are needed only on a raise.
 template <bool kMasked, typename OkFn, int kNst = 4>
-SC_DEV void softmax_tile2(const bf16x8 (&qf)[kSub1][2], const __bf16* sK, const __bf16* sV, float c2, int lr,
-                          int g, float (&m_use)[kSub1], float (&l_run)[kSub1], f32x4 (&o)[kSub1][4], unsigned live,
+SC_DEV void softmax_tile2(const bf16x8 (&qf)[2], const __bf16* sK, const __bf16* sV, float c2, int lr,
+                          int g, float& m_use, float& l_run, f32x4 (&o)[4], unsigned live,
                           OkFn ok) {
-  f32x4 s[kSub1][4];
+  f32x4 s[4];
   qk_tile2<kMasked, kNst>(qf, sK, lr, g, live, s);
   if constexpr (kMasked) {
-#pragma unroll
-    for (int j = 0; j < kSub1; ++j)
 #pragma unroll
       for (int st = 0; st < kNst; ++st)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          s[j][st][i] = (((live >> st) & 1u) && ok(j, st, i)) ? s[j][st][i] : -INFINITY;
+          s[st][i] = (((live >> st) & 1u) && ok(st, i)) ? s[st][i] : -INFINITY;
   }
-  bf16x8 pb[kSub1][2];
-  float part[kSub1];
+  bf16x8 pb[2];
+  float part;
   exp_tile2<kNst>(s, c2, m_use, pb, part);
-  bool over = false;
-#pragma unroll
-  for (int j = 0; j < kSub1; ++j) over |= part[j] > kRaiseSum;
-  if (__builtin_amdgcn_ballot_w64(over) != 0ull) {
-    float lmax[kSub1];
+  if (__builtin_amdgcn_ballot_w64(part > kRaiseSum) != 0ull) {
+    float lmax;
     lane_max2<kNst>(s, lmax);
     raise2(lmax, c2, m_use, l_run, o);
     exp_tile2<kNst>(s, c2, m_use, pb, part);
   }
-#pragma unroll
-  for (int j = 0; j < kSub1; ++j) l_run[j] += part[j];
+  l_run += part;
   pv_tile2<kMasked, kNst>(pb, sV, o, live);
 }
 
@@ -959,14 +926,13 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
   tile_dma(Vg, ldb, sm.c[0], w, lane, band_rows(kt0));
   // query fragments straight from HBM (rows clamped below L; same dims per
   // lane group as the key fragments)
-  constexpr int kWQ = 16 * kSub1;  // queries per wave
+  constexpr int kWQ = 16;  // queries per wave
   const int qa = q0 + kWQ * w;
-  bf16x8 qf[kSub1][2];
-#pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    const T* qrow = Qg + (long long)min(qa + 16 * j + lr, L - 1) * ld;
-    qf[j][0] = *reinterpret_cast<const bf16x8*>(qrow + 8 * g);
-    qf[j][1] = *reinterpret_cast<const bf16x8*>(qrow + 32 + 8 * g);
+  bf16x8 qf[2];
+  {
+    const T* qp = Qg + (long long)min(qa + lr, L - 1) * ld;
+    qf[0] = *reinterpret_cast<const bf16x8*>(qp + 8 * g);
+    qf[1] = *reinterpret_cast<const bf16x8*>(qp + 32 + 8 * g);
   }
   // bitmask of in-band global keys, the list of 64-slot chunks with keys
   // outside [kt0, kt1), and the first listed chunk compacted into sm.pos[1]
@@ -1008,15 +974,10 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
     return cnt;
   };
   const int gcnt0 = hasg ? sm.misc[2] : 0;
-  float m_use[kSub1], l_run[kSub1];
-  f32x4 o[kSub1][4];
+  float m_use = kNegBig, l_run = 0.f;
+  f32x4 o[4];
 #pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    m_use[j] = kNegBig;
-    l_run[j] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) o[j][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int dt = 0; dt < 4; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   // all vector loads so far (the first tiles, the query fragments) complete
   // here; the compiler-visible wait keeps it from waiting for the query loads
   // inside the tile loop, where the prefetch loads are in flight
@@ -1028,23 +989,17 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
   // block are listed); half a tile when they fit in 32 rows
   auto glob_tile = [&](int buf, int cnt) {
     const unsigned live = (cnt > 0 ? 1u : 0u) | (cnt > 16 ? 2u : 0u) | (cnt > 32 ? 4u : 0u) | (cnt > 48 ? 8u : 0u);
-    auto ok = [&](int, int st, int i) { return 16 * st + 4 * g + i < cnt; };
+    auto ok = [&](int st, int i) { return 16 * st + 4 * g + i < cnt; };
     if (cnt <= 32)
       softmax_tile2<true, decltype(ok), 2>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live, ok);
     else
       softmax_tile2<true, decltype(ok), 4>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live, ok);
   };
 
-  // per-lane band bounds of sub-block j relative to a tile start, shifted by
+  // per-lane band bounds relative to a tile start, shifted by
   // the lane group's key offset 4g: key 16st + i of the lane is allowed when
   // it lies in [lo - k0, hi - k0]
-  int lo[kSub1], hi[kSub1];
-#pragma unroll
-  for (int j = 0; j < kSub1; ++j) {
-    const int q = qa + 16 * j + lr;
-    lo[j] = q - r - 4 * g;
-    hi[j] = min(q + rh, kt1 - 1) - 4 * g;
-  }
+  const int lo = qa + lr - r - 4 * g, hi = min(qa + lr + rh, kt1 - 1) - 4 * g;
   // Pipeline steps: band tile 0, then (hasg) the first gathered global chunk,
   // then band tiles 1 .. nkt-1; step s computes from buffer s & 1 while the
   // next step's data arrive in the other.  Band tile t therefore lives in
@@ -1077,34 +1032,29 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
 #pragma unroll
     for (int st = 0; st < 4; ++st)
       live |= (unsigned)((16 * st + 15 >= wlo && 16 * st <= whi) || ((gall >> (16 * st)) & 0xFFFFull) != 0ull) << st;
-    int lt[kSub1], ht[kSub1];
-#pragma unroll
-    for (int j = 0; j < kSub1; ++j) {
-      lt[j] = lo[j] - k0;
-      ht[j] = hi[j] - k0;
-    }
+    const int lt = lo - k0, ht = hi - k0;
     // a band edge is one-sided in most tiles: the band starts inside the
     // tile for some query (nlo) or ends inside it (nhi), wave-uniform
     const bool nlo = qa + kWQ - 1 - r - k0 > 0, nhi = min(qa + rh, kt1 - 1) - k0 < kBK - 1;
     if (gall == 0ull && !nhi) {
       softmax_tile2<true>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live,
-                          [&](int j, int st, int i) { return 16 * st + i >= lt[j]; });
+                          [&](int st, int i) { return 16 * st + i >= lt; });
     } else if (gall == 0ull && !nlo) {
       softmax_tile2<true>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live,
-                          [&](int j, int st, int i) { return 16 * st + i <= ht[j]; });
+                          [&](int st, int i) { return 16 * st + i <= ht; });
     } else if (gall == 0ull) {
-      softmax_tile2<true>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live, [&](int j, int st, int i) {
+      softmax_tile2<true>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live, [&](int st, int i) {
         const int c = 16 * st + i;
-        return (c >= lt[j]) & (c <= ht[j]);
+        return (c >= lt) & (c <= ht);
       });
     } else {
       const unsigned long long gm = gall >> (4 * g);
       // a global key is attended by every query, or (causal) by the queries
       // at or after it
-      softmax_tile2<true>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live, [&](int j, int st, int i) {
+      softmax_tile2<true>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, live, [&](int st, int i) {
         const int c = 16 * st + i;
-        const bool band = (c >= lt[j]) & (c <= ht[j]);
-        return band | (((gm >> c) & 1ull) != 0ull && c <= (causal ? ht[j] : 1 << 30));
+        const bool band = (c >= lt) & (c <= ht);
+        return band | (((gm >> c) & 1ull) != 0ull && c <= (causal ? ht : 1 << 30));
       });
     }
   };
@@ -1116,7 +1066,7 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
   auto interior_tile = [&](int t) {
     const int buf = bufof(t);
     softmax_tile2<false>(qf, sm.b[buf], sm.c[buf], a.c2, lr, g, m_use, l_run, o, 0xFu,
-                         [](int, int, int) { return true; });
+                         [](int, int) { return true; });
   };
   // step 0: band tile 0 (interior for this wave only when ia == 0 < ib)
   // while the global chunk's gather (or band tile 1) arrives
@@ -1164,12 +1114,11 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
     __syncthreads();
   }
 
-  static_assert(kSub1 == 1, "the rows' staging holds one sub-block per wave");
-  const float l_row = group_sum(l_run[0]);
+  const float l_row = group_sum(l_run);
   const int qrow = qa + lr;
   const bool qin = qrow < L;
   const bool qvalid = qin && !gbit(qrow);  // qrow in [q0, L) lies inside [kt0, kt1)
-  const float lse2 = m_use[0] + fast_log2(l_row);
+  const float lse2 = m_use + fast_log2(l_row);
   const float inv = 1.0f / l_row;
   // the wave's 16 rows leave through its part of the (free) key tiles, a whole
   // 128-byte row per 8 lanes instead of 32-byte runs of 16 rows (launch 1 of
@@ -1180,8 +1129,8 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) {
     uint2 x;
-    x.x = qin ? pack_bf16(o[0][dt][0] * inv, o[0][dt][1] * inv) : 0u;
-    x.y = qin ? pack_bf16(o[0][dt][2] * inv, o[0][dt][3] * inv) : 0u;
+    x.x = qin ? pack_bf16(o[dt][0] * inv, o[dt][1] * inv) : 0u;
+    x.y = qin ? pack_bf16(o[dt][2] * inv, o[dt][3] * inv) : 0u;
     *reinterpret_cast<uint2*>(st + 128 * lr + 16 * ((2 * dt + (g >> 1)) ^ (lr & 7)) + 8 * (g & 1)) = x;
   }
 #pragma unroll
