@@ -1148,11 +1148,15 @@ SC_DEV void window_fwd_v2(const AttnArgs& a, int bh, int qb, Smem<1>& sm, uint32
 // A wave owns 32 queries and takes a tile's keys in halves of 32 on the 32x32x16
 // products: against 16 queries a wave, each K fragment and V read feeds twice
 // the pairs, and the tile's address, load and max bookkeeping is spread over
-// twice as many.  The interior loop issues 3.3 VALU instructions per pair
-// and lane (an FMA, an exponential, an add, half a conversion), so it runs near
-// the VALU issue rate at three waves per SIMD (166 VGPRs); four waves per SIMD
-// (128 VGPRs, addresses recomputed) measured the same.  What is left is the
-// launch's tail (3.2 rounds of 20 us blocks at B8 n4096).
+// twice as many.  Counters at B8 H12 n4096 with full lengths and no global
+// keys, window 512, 1024 and 2048: 23.4M, 38.5M and 65.6M VALU instructions.  That
+// is 5.3 per 64 pairs (an FMA, an exponential, an add and half a conversion make
+// 3.5, the products 0.5, addresses, reads and the raise's test the rest) and
+// 7.1M beside the pairs (edge halves, prologue, epilogue).  64 more pairs cost a
+// SIMD 34 cycles, beside 23 of VALU issue and 16 of MFMA, which overlap.  Over the
+// launch at window 512 (2048) VALU is busy 0.51 (0.63) of the cycles, MFMA 0.24
+// (0.36), and waves wait 25 % (32 %) of their time: latency at three waves per
+// SIMD, and the launch's tail (3.2 rounds of 20 us blocks at B8 n4096).
 constexpr int kBQ3 = 128;  // queries per block: 4 waves x 32
 
 // Logits of keys 32 h .. 32 h + 31 of a tile: S^T = K Q^T.  Lane l holds query
